@@ -1,5 +1,6 @@
 // libauv: environment kernels (reset, lane-per-environment step loop, statistics,
 // GAE) and the C interface.  The policy-driven fused rollout lives in auv_policy.hip.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -260,119 +261,81 @@ __global__ __launch_bounds__(64 * RED_WAVES) void k_stats_reduce(const float* __
   }
 }
 
-// Backward GAE scan, one lane per environment, [T][N] layout (coalesced over envs).
-// Streams the steps backwards in chunks of GAE_CHUNK with the next chunk's loads issued
-// before the current chunk is scanned, so about 2 x 3 x GAE_CHUNK loads per lane are in
-// flight (the scan is HBM-bound: 20 B per env-step).
-constexpr int GAE_CHUNK = 32;
-
-struct GaeChunk { float r[GAE_CHUNK], v[GAE_CHUNK], d[GAE_CHUNK]; };
-
-__device__ __forceinline__ void gae_load(GaeChunk& c, int t0, int t1, size_t N, int i, const float* __restrict__ rew,
-                                         const float* __restrict__ val, const float* __restrict__ dn) {
-#pragma unroll
-  for (int k = 0; k < GAE_CHUNK; ++k) {
-    const int t = t0 + k;
-    if (t < t1) {
-      const size_t ti = (size_t)t * N + i;
-      c.r[k] = rew[ti];
-      c.v[k] = val[ti];
-      c.d[k] = dn[ti];
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void k_gae(int T, int n, const float* __restrict__ rew,
-                                             const float* __restrict__ val, const float* __restrict__ dn,
-                                             const float* __restrict__ last, float gamma, float gl,
-                                             float* __restrict__ adv, float* __restrict__ ret) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const size_t N = (size_t)n;
-  float next_v = last[i], next_a = 0.0f;
-  int t1 = T, t0 = T > GAE_CHUNK ? T - GAE_CHUNK : 0;
-  GaeChunk cur, nxt;
-  gae_load(cur, t0, t1, N, i, rew, val, dn);
-  while (t1 > 0) {
-    const int u1 = t0, u0 = u1 > GAE_CHUNK ? u1 - GAE_CHUNK : 0;
-    if (u1 > 0) gae_load(nxt, u0, u1, N, i, rew, val, dn);
-#pragma unroll
-    for (int k = GAE_CHUNK - 1; k >= 0; --k) {
-      const int t = t0 + k;
-      if (t < t1) {
-        const float nd = 1.0f - cur.d[k];
-        const float delta = cur.r[k] + gamma * nd * next_v - cur.v[k];
-        next_a = delta + gl * nd * next_a;
-        const size_t ti = (size_t)t * N + i;
-        adv[ti] = next_a;
-        ret[ti] = next_a + cur.v[k];
-        next_v = cur.v[k];
-      }
-    }
-    cur = nxt;
-    t1 = u1;
-    t0 = u0;
-  }
-}
-
-// Segmented backward GAE for T <= 16 L.  The recursion A_t = delta_t + c_t A_{t+1}, with
-// c_t = gamma lambda (1 - d_t) and delta_t = r_t + gamma (1 - d_t) V_{t+1} - V_t, is linear in
-// A: over a segment of steps [t0, t1) it gives A_t = alpha_t + beta_t A_{t1}, alpha from the
-// recursion started at 0, beta_t = c_t ... c_{t1-1}.  Wave w of a workgroup takes segment w
-// (L steps) of the workgroup's 64 environments, so the scan of one environment is spread over
-// up to 16 waves and every load is issued at once; the waves exchange (alpha, beta) of their
-// first step through LDS, and each folds the later segments, last one first, into the A that
-// enters its own segment.  Same arithmetic per step as k_gae; the fold adds one multiply-add.
-template <int L>
+// Segmented backward GAE.  The recursion A_t = delta_t + c_t A_{t+1}, with c_t = gamma lambda
+// (1 - d_t) and delta_t = r_t + gamma (1 - d_t) V_{t+1} - V_t, is linear in A: over a segment
+// of steps [t0, t1) it gives A_t = alpha_t + beta_t A_{t1}, alpha from the recursion started
+// at 0, beta_t = c_t ... c_{t1-1}.  A workgroup takes E environments (lane mod E) and, per
+// round, S = (64 / E) waves segments of L steps each, so that the scan of one environment is
+// spread over many lanes and every load of a round is issued at once; the segments exchange
+// (alpha, beta) of their first step through LDS, and each folds the later segments, last one
+// first, into the A that enters its own.  Rounds run from the last steps to the first; the A
+// that leaves a round (the same fold carried on to segment 0) enters the one before it.
+// Bound by HBM (20 B per environment-step): 4096 x 1000 in 20 us, 4.1 TB/s; one lane per
+// environment with the scan's steps in series, which this replaced above 512 steps, took 117 us.
+template <int L, int E>
 __global__ __launch_bounds__(1024) void k_gae_seg(int T, int n, const float* __restrict__ rew,
                                                   const float* __restrict__ val, const float* __restrict__ dn,
                                                   const float* __restrict__ last, float gamma, float gl,
                                                   float* __restrict__ adv, float* __restrict__ ret) {
-  __shared__ float2 pair[16][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, S = blockDim.x >> 6;
-  const int i = blockIdx.x * 64 + lane;
+  constexpr int SPW = 64 / E;                // segments per wave
+  __shared__ float2 pair[2][16 * SPW][E];    // by round parity: read in a round, written again two rounds on
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, S = SPW * (blockDim.x >> 6);
+  const int e = lane % E, seg = SPW * w + lane / E;
+  const int i = blockIdx.x * E + e;
   const bool valid = i < n;
   const size_t N = (size_t)n, ic = (size_t)(valid ? i : n - 1);
-  const int t0 = w * L, t1 = min(T, t0 + L);
-  float r[L], v[L], d[L];
+  const int span = S * L;
+  float carry = 0.0f;                        // A entering the round from the later steps
+  for (int round = (T - 1) / span; round >= 0; --round) {
+    const int t0 = round * span + seg * L, t1 = min(T, t0 + L);
+    float r[L], v[L], d[L];
 #pragma unroll
-  for (int k = 0; k < L; ++k) {   // unconditional loads from clamped steps: all in flight at once
-    const size_t ti = (size_t)min(t0 + k, T - 1) * N + ic;
-    r[k] = rew[ti];
-    v[k] = val[ti];
-    d[k] = dn[ti];
-  }
-  float vnext = t1 < T ? val[(size_t)t1 * N + ic] : last[ic];
-  float a = 0.0f, b = 1.0f;
-#pragma unroll
-  for (int k = L - 1; k >= 0; --k) {
-    if (t0 + k < t1) {
-      const float nd = 1.0f - d[k];
-      const float delta = r[k] + gamma * nd * vnext - v[k];
-      const float c = gl * nd;
-      a = delta + c * a;
-      b = c * b;
-      vnext = v[k];
+    for (int k = 0; k < L; ++k) {   // unconditional loads from clamped steps: all in flight at once
+      const size_t ti = (size_t)min(t0 + k, T - 1) * N + ic;
+      r[k] = rew[ti];
+      v[k] = val[ti];
+      d[k] = dn[ti];
     }
-    r[k] = a;   // alpha_t
-    d[k] = b;   // beta_t
-  }
-  pair[w][lane] = make_float2(a, b);
-  __syncthreads();
-  float ain = 0.0f;
-  for (int s2 = S - 1; s2 > w; --s2) {
-    const float2 q = pair[s2][lane];
-    ain = q.x + q.y * ain;
-  }
-  if (valid) {
+    float vnext = t1 < T ? val[(size_t)t1 * N + ic] : last[ic];
+    float a = 0.0f, b = 1.0f;
 #pragma unroll
-    for (int k = 0; k < L; ++k)
+    for (int k = L - 1; k >= 0; --k) {
       if (t0 + k < t1) {
-        const size_t ti = (size_t)(t0 + k) * N + i;
-        const float A = r[k] + d[k] * ain;
-        adv[ti] = A;
-        ret[ti] = A + v[k];
+        const float nd = 1.0f - d[k];
+        const float delta = r[k] + gamma * nd * vnext - v[k];
+        const float c = gl * nd;
+        a = delta + c * a;
+        b = c * b;
+        vnext = v[k];
       }
+      r[k] = a;   // alpha_t
+      d[k] = b;   // beta_t
+    }
+    float2(*P)[E] = pair[round & 1];
+    P[seg][e] = make_float2(a, b);
+    __syncthreads();
+    float ain = carry;
+    for (int s2 = S - 1; s2 > seg; --s2) {
+      const float2 q = P[s2][e];
+      ain = q.x + q.y * ain;
+    }
+    if (round > 0) {
+      carry = ain;
+      for (int s2 = seg; s2 >= 0; --s2) {
+        const float2 q = P[s2][e];
+        carry = q.x + q.y * carry;
+      }
+    }
+    if (valid) {
+#pragma unroll
+      for (int k = 0; k < L; ++k)
+        if (t0 + k < t1) {
+          const size_t ti = (size_t)(t0 + k) * N + i;
+          const float A = r[k] + d[k] * ain;
+          adv[ti] = A;
+          ret[ti] = A + v[k];
+        }
+    }
   }
 }
 
@@ -785,19 +748,23 @@ int auv_gae(int32_t T, int32_t n_envs, const float* reward, const float* value, 
   if (!std::isfinite(gamma) || !std::isfinite(lambda))
     return set_error(AUV_EINVAL, "auv_gae: gamma and lambda must be finite");
   hipStream_t s = (hipStream_t)stream;
-  const int groups = (n_envs + 63) / 64;
-  if (T <= 16 * 16) {
-    const int S = (T + 15) / 16;
-    hipLaunchKernelGGL(k_gae_seg<16>, dim3(groups), dim3(64 * S), 0, s, T, n_envs, reward, value, done, last_value,
-                       gamma, gamma * lambda, adv, ret);
-  } else if (T <= 16 * 32) {
-    const int S = (T + 31) / 32;
-    hipLaunchKernelGGL(k_gae_seg<32>, dim3(groups), dim3(64 * S), 0, s, T, n_envs, reward, value, done, last_value,
-                       gamma, gamma * lambda, adv, ret);
-  } else {
-    hipLaunchKernelGGL(k_gae, dim3((n_envs + 255) / 256), dim3(256), 0, s, T, n_envs, reward, value, done,
-                       last_value, gamma, gamma * lambda, adv, ret);
-  }
+  const float gl = gamma * lambda;
+  auto launch = [&](auto kernel, int L, int E) {
+    const int spw = 64 / E, waves = std::min(16, (T + L * spw - 1) / (L * spw));
+    hipLaunchKernelGGL(kernel, dim3((n_envs + E - 1) / E), dim3(64 * waves), 0, s, T, n_envs, reward, value, done,
+                       last_value, gamma, gl, adv, ret);
+  };
+  // 64 environments per workgroup read whole 256-byte rows and win once that gives every CU a
+  // workgroup (16384 x 1000: 62 us, with 32 per workgroup 71 us); below, 32 give twice the
+  // workgroups and twice the segments (4096 x 1000: 20 us against 24; 4096 x 512: 9.2 against
+  // 12.6), and 16 the shortest scan of a few environments (64 x 4000: 23 us against 38; at 512 x
+  // 2000 no longer faster).  Segments of 32 steps were slower everywhere (4096 x 1000: 28-40 us).
+  if (n_envs >= 64 * compute_units())
+    launch(k_gae_seg<16, 64>, 16, 64);
+  else if (n_envs > 256)
+    launch(k_gae_seg<16, 32>, 16, 32);
+  else
+    launch(k_gae_seg<16, 16>, 16, 16);
   return check_launch("auv_gae");
 }
 

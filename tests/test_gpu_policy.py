@@ -348,3 +348,24 @@ def test_two_tile_rollout_parity(nets):
         worst = _teacher_forced(cfg, got, off, 64, T)
         announce(f"  envs {off}..{off + 63}: state {worst[0]:.2e} reward {worst[1]:.2e} obs {worst[2]:.2e}")
         assert worst[3] == 0 and worst[0] <= 1e-4 and worst[1] <= 1e-4 and worst[2] <= 1e-4
+
+
+@pytest.mark.parametrize("n,T", [(1, 1), (256, 1025), (16, 2049), (257, 512), (300, 513), (1000, 1100), (16385, 256),
+                                 (16384, 257)])
+def test_gae_sizes(n, T):
+    """Each number of environments per workgroup (16, 32, 64) at and past one round of the
+    segmented scan, against the oracle.  Every step adds at most six roundings of values within
+    the result's scale, and each decays by gamma lambda, so 6 x 2^-24 / (1 - 0.9405) of it."""
+    from paper_2512_13359_amd import _abi as A
+    announce(f"gae n={n} T={T}")
+    r = np.random.default_rng(n + T)
+    x = dict(reward=r.standard_normal((T, n)), value=3 * r.standard_normal((T, n)), done=r.random((T, n)) < 0.01,
+             last=r.standard_normal(n))
+    x = {k: v.astype(np.float32) for k, v in x.items()}
+    d = {k: torch.from_numpy(v).cuda() for k, v in x.items()}
+    adv, ret = (torch.full((T, n), float("nan"), device="cuda") for _ in range(2))
+    A.auv_gae(T, n, d["reward"], d["value"], d["done"], d["last"], 0.99, 0.95, adv, ret)
+    a, q = ogae.gae(x["reward"], x["value"], x["done"], x["last"], np.float32(0.99), np.float32(0.95))
+    bound = 6 * 2.0 ** -24 / (1 - 0.9405) * max(np.abs(a).max(), np.abs(q).max(), np.abs(x["value"]).max())
+    assert np.abs(host(adv) - a).max() <= bound
+    assert np.abs(host(ret) - q).max() <= bound
