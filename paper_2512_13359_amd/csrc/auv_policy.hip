@@ -395,6 +395,12 @@ __global__ __launch_bounds__(rollout_threads<TPW>(), 1) void k_policy_rollout(Ve
 // group's inputs are loaded while this group's layers 2 and 3 run.
 constexpr int MLPW_WAVES = 8;
 constexpr int MLPW_NT = 2;   // 16-sample tiles per wave and group
+// Groups a workgroup is launched for: one wave per SIMD while there are CUs left (20011 samples:
+// 9 us of kernel instead of 28 with the staging below; with all eight waves of fewer workgroups
+// 13.5 us; fewer than four gained nothing, the weights' staging being the rest).
+constexpr int MLPW_SHARE = 4;
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 struct MlpWideShared {
   bf16x8 w1[16][64];      // layer 1 [M-tile][lane] (K = the 32 padded inputs)
@@ -417,35 +423,59 @@ __global__ __launch_bounds__(64 * MLPW_WAVES, 2) void k_mlp(const uint16_t* __re
     const uint16_t* W1 = w;
     const uint16_t* W2 = w + HID * 23;
     const uint16_t* W3 = W2 + HID * HID;
-    constexpr int F1 = 16, F2 = 16 * 8, F3 = 8;
-    for (int e = tid; e < (F1 + F2 + F3) * 64; e += 64 * MLPW_WAVES) {
-      const int f = e >> 6, l = e & 63, lg = l >> 4, lr = l & 15;
+    // Every load is issued before the first LDS store, so that a workgroup waits for memory once
+    // (a loop of load-then-store over the fragments waited 19 times: 20 us of the kernel at any
+    // size).  W2 is read in 16-byte pieces of whole rows; the piece of row 16 mt + r at columns
+    // 32 kt + o .. + 7 (o = 0, 8, 16, 24) is the half o / 16 (K slots 4 (o / 16) .. + 3) of lanes
+    // 16 g + r and 16 (g + 1) + r, g = (o % 16) / 4.
+    constexpr int NT = 64 * MLPW_WAVES, P2 = HID * HID / 8 / NT, P1 = 16 * 64 / NT;
+    u32x4 v2[P2];
+    uint16_t v1[P1][8], v3[8];
+#pragma unroll
+    for (int q = 0; q < P2; ++q) {
+      const int e = tid + q * NT;
+      v2[q] = *reinterpret_cast<const u32x4*>(W2 + (e >> 5) * HID + 8 * (e & 31));
+    }
+#pragma unroll
+    for (int q = 0; q < P1; ++q) {
+      const int e = tid + q * NT, f = e >> 6, l = e & 63;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v1[q][j] = W1[(16 * f + (l & 15)) * 23 + min(kslot(l >> 4, j), 22)];
+    }
+    const int k3 = tid >> 6, g3 = (tid >> 4) & 3, r3 = tid & 15;   // one layer-3 slot per thread
+    {
+      const uint16_t* p = W3 + min(r3, n_out - 1) * HID + 32 * k3 + 4 * g3;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v3[j] = p[16 * (j >> 2) + (j & 3)];
+    }
+    const float bb1 = b[tid & (HID - 1)], bb2 = b[HID + (tid & (HID - 1))], bb3 = b[2 * HID + min(tid, n_out - 1)];
+#pragma unroll
+    for (int q = 0; q < P2; ++q) {
+      const int e = tid + q * NT, rw = e >> 5, c = 8 * (e & 31);
+      const int o = c & 31, g0 = (o & 15) >> 2, rr = rw & 15;
+      char* frag = reinterpret_cast<char*>(&S.w2[rw >> 4][c >> 5][0]) + 8 * (o >> 4);
+      *reinterpret_cast<uint2*>(frag + 16 * (16 * g0 + rr)) = uint2{v2[q].x, v2[q].y};
+      *reinterpret_cast<uint2*>(frag + 16 * (16 * (g0 + 1) + rr)) = uint2{v2[q].z, v2[q].w};
+    }
+#pragma unroll
+    for (int q = 0; q < P1; ++q) {
+      const int e = tid + q * NT, f = e >> 6, l = e & 63;
       bf16x8 v;
-      if (f < F1) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int k = kslot(lg, j);
-          v[j] = k < 23 ? bf16_of_bits(W1[(16 * f + lr) * 23 + k]) : bf16_of_bits(0);
-        }
-        S.w1[f][l] = v;
-      } else if (f < F1 + F2) {
-        const int mt = (f - F1) >> 3, kt = (f - F1) & 7;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = bf16_of_bits(W2[(16 * mt + lr) * HID + 32 * kt + kslot(lg, j)]);
-        S.w2[mt][kt][l] = v;
-      } else {
-        const int kt = f - F1 - F2;
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          v[j] = lr < n_out ? bf16_of_bits(W3[lr * HID + 32 * kt + kslot(lg, j)]) : bf16_of_bits(0);
-        S.w3[kt][l] = v;
-      }
+      for (int j = 0; j < 8; ++j) v[j] = bf16_of_bits(kslot(l >> 4, j) < 23 ? v1[q][j] : (uint16_t)0);
+      S.w1[f][l] = v;
     }
-    for (int i = tid; i < HID; i += 64 * MLPW_WAVES) {
-      S.b1k[i] = b[i] * TWO_LOG2E;
-      S.b2k[i] = b[HID + i] * TWO_LOG2E;
+    {
+      bf16x8 v;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = bf16_of_bits(r3 < n_out ? v3[j] : (uint16_t)0);
+      S.w3[k3][tid & 63] = v;
     }
-    if (tid < 16) S.b3[tid] = tid < n_out ? b[2 * HID + tid] : 0.0f;
+    if (tid < HID) {
+      S.b1k[tid] = bb1 * TWO_LOG2E;
+      S.b2k[tid] = bb2 * TWO_LOG2E;
+    }
+    if (tid < 16) S.b3[tid] = tid < n_out ? bb3 : 0.0f;
   }
   __syncthreads();
 
@@ -466,7 +496,7 @@ __global__ __launch_bounds__(64 * MLPW_WAVES, 2) void k_mlp(const uint16_t* __re
     }
     return x;
   };
-  int grp = blockIdx.x * MLPW_WAVES + wave;
+  int grp = wave * gridDim.x + blockIdx.x;   // over the workgroups first, then over their waves
   XRaw xr = load_x(min(grp, groups - 1));
   for (; grp < groups; grp += stride) {
     bf16x8 x[MLPW_NT];
@@ -539,7 +569,7 @@ static int check_mlp(const auv_mlp* net, int n_out_want, const char* what) {
 
 static int mlp_grid(int n) {   // one workgroup per CU (its weights fill the LDS)
   const int groups = ((n + 15) / 16 + MLPW_NT - 1) / MLPW_NT;
-  const int wgs = (groups + MLPW_WAVES - 1) / MLPW_WAVES;
+  const int wgs = (groups + MLPW_SHARE - 1) / MLPW_SHARE;
   const int cus = compute_units();
   return wgs < cus ? wgs : cus;
 }

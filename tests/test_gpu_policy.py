@@ -369,3 +369,24 @@ def test_gae_sizes(n, T):
     bound = 6 * 2.0 ** -24 / (1 - 0.9405) * max(np.abs(a).max(), np.abs(q).max(), np.abs(x["value"]).max())
     assert np.abs(host(adv) - a).max() <= bound
     assert np.abs(host(ret) - q).max() <= bound
+
+
+@pytest.mark.parametrize("n_out", [1, 8])
+def test_mlp_forward_independent_of_batch(n_out):
+    """A sample's output has the same bits in a batch that gives every wave several groups as in
+    batches of less than a tile, of a ragged tile and of one group per workgroup."""
+    from paper_2512_13359_amd import _abi as A, upload_mlp
+    announce(f"mlp forward slices n_out={n_out}")
+    net = upload_mlp(W.mlp_weights(n_out, 5))
+    n = 140013
+    obs = torch.from_numpy(np.random.default_rng(1).uniform(-2, 2, (23, n)).astype(np.float32)).cuda()
+
+    def forward(o):
+        out = torch.full((n_out, o.shape[1]), float("nan"), device="cuda")
+        A.auv_mlp_forward(net["struct"], o.shape[1], o, out)
+        return out
+
+    full = forward(obs)
+    assert torch.isfinite(full).all()
+    for a, b in [(0, 7), (7, 40), (40, 40 + 130), (1000, 1000 + 8191), (9000, 9000 + 32769), (n - 19, n)]:
+        assert torch.equal(forward(obs[:, a:b].contiguous()), full[:, a:b]), (a, b)
