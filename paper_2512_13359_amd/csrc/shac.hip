@@ -8,24 +8,27 @@
 //   k_frags        the bf16 weights of each network rearranged into the MFMA A fragments
 //                  that the window kernel reads (W1, W2, W3 and their transposes)
 //   k_window<mode> one workgroup of four waves per 16 environments, the whole window in one
-//                  launch.  Every wave steps the physics of all 16 environments (lane r and
-//                  its copies r + 16, r + 32, r + 48 hold environment r), so each wave has
-//                  the observations, actions and adjoints it needs without an exchange;
-//                  the networks are split by hidden feature, wave w owning features
-//                  64 w .. 64 w + 63 of both hidden layers (its 64 rows of W2, then of W2^T,
-//                  in LDS; its small weights in registers).  At workgroup barriers the waves
-//                  exchange through LDS only hidden layer 1 and the output partials (two
-//                  barriers per forward step), q(dz2) and the input-gradient partials (two
-//                  per reverse step).  Forward sweep: policy on MFMA, RK4 of the paper
-//                  task, reward, checkpoints of every step's state, RK4 substep start
-//                  states and action average, every wave's hidden-2 activations; terminal
+//                  launch.  Every wave steps the physics of all 16 environments, four lanes
+//                  per environment (shac_quad.hpp), so each wave has the observations, actions
+//                  and adjoints it needs without an exchange; the networks are split by hidden
+//                  feature, wave w owning features 64 w .. 64 w + 63 of both hidden layers (its
+//                  64 rows of W2, then of W2^T, in LDS; its small weights in registers).  At
+//                  workgroup barriers the waves exchange through LDS only hidden layer 1 and
+//                  the output partials (two barriers per forward step), q(dz2) and the
+//                  input-gradient partials (two per reverse step).  Forward sweep: policy on
+//                  MFMA, RK4 of the paper task, reward, and what the reverse sweep needs (every
+//                  RK4 stage's input, the observation with the factors of its derivative, the
+//                  action and its moving average, every wave's hidden-2 activations); terminal
 //                  value and its input gradient; the environment update (reset where the
 //                  window ends the episode); reverse sweep: per step, the state adjoint
-//                  through reward, observation and RK4 (shac_adjoint.hpp; each substep's
-//                  adjoint starts from its stored start state), the clip, and the policy's
-//                  input gradient (backward on MFMA from the stored hidden-2 activations).  Each
-//                  wave stores the bf16 operands of the weight gradient of its features
-//                  (q(h1), q(h2), q(dz2), q(dz1); wave 0 also q(o), q(gy)) as "half
+//                  through RK4 from the stored stage inputs, the clip, the policy's input
+//                  gradient (backward on MFMA from the stored hidden-2 activations), and one
+//                  observation adjoint that takes the policy's and the reward's cotangents
+//                  together.  Bound by the instruction stream of one wave per SIMD (at 4096
+//                  environments every CU holds one workgroup): with the physics in one-lane
+//                  form, every lane row a copy, and the RK4 stages re-integrated in the
+//                  reverse sweep, a 32-step window took 693 us in all; as it is, 457 us.  Each wave stores the bf16 operands of the weight gradient of its
+//                  features (q(h1), q(h2), q(dz2), q(dz1); wave 0 also q(o), q(gy)) as "half
 //                  fragments"
 //   k_dw2          (PPO update) dW2 = sum q(dz2) q(h1)^T over all N h samples
 //   k_wsmall       dW1, dW3, the bias gradients and d log_std, per workgroup
@@ -42,7 +45,7 @@
 
 #include "auv_internal.hpp"
 #include "mlp_mfma.hpp"
-#include "shac_adjoint.hpp"
+#include "shac_quad.hpp"
 
 namespace auv {
 namespace shac {
@@ -55,7 +58,6 @@ constexpr int WF = 32;                   // W2 (or W2^T) fragments of one wave: 
 constexpr int MAX_H = 64;                // window length bound
 constexpr int MAX_S = 4;                 // RK4 substeps per control step bound
 constexpr int TS = 20;                   // bf16 row stride of a transpose buffer
-constexpr int CK = 19;                   // checkpoint rows: state (13) and action average (6)
 constexpr int MODE_EXTERNAL = 0, MODE_MEAN = 2, MODE_SAMPLE = 3;
 
 // Fragment arrays of one network, in 64-lane fragments of 16 bytes per lane.
@@ -80,7 +82,11 @@ struct WinArgs {
   float gamma;
   NetF pol, val;
   const float* log_std;
-  float *ck, *sub, *acts, *J, *Jr, *vl, *gls;     // sub: RK4 substep start states [h][MAX_S - 1][13][Np]
+  // per lane of the four-lane layout, [..][workgroup][lane]: rec [h][substeps][4 RK4 stages]
+  // (q, v, omega, and p in the first, 1 / |q| in the last), obk [h] (dpb, rotation vector, sk, kn), aa [h] (action components c and 3 + c
+  // before clipping, their moving averages before the step)
+  f32x4 *rec, *obk, *aa;
+  float *J, *Jr, *vl, *gls;
   f32x4* h2s;                          // policy hidden-2 activations [h][G][wave][M-tile][lane]
   u32x2 *x_half, *h1_half, *h2_half, *gy_half, *dz2_half, *dz1_half;
   int Np;
@@ -90,13 +96,14 @@ struct WinArgs {
 
 struct Lds {
   bf16x8 W[WAVES][WF][64];    // per wave: its W2 fragments (forward sweep), then its W2^T ones (reverse)
-  __bf16 X[WAVES][EPG][32];   // per wave: layer-1 inputs of the 16 environments
+  __bf16 X[WAVES][EPG][16];   // per wave: layer-1 inputs of the 16 environments (12 used, the rest zero)
   __bf16 G[WAVES][EPG][8];    // per wave: q(dL/dy)
   __bf16 T[WAVES][32 * TS];   // per wave: transpose buffer [feature][environment]
   float Y[2][WAVES][EPG][8];  // output partials of each wave (two buffers, alternate steps)
   bf16x8 DZ[8][64];           // a B operand of all 256 hidden features (K step s: 32 s ..): hidden 1
                               // (forward), q(dz2) (reverse)
   float GX[WAVES][EPG][16];   // input-gradient partials of each wave (inputs 0..15)
+  float pw[MAX_H + 1];        // gamma^t
 };
 static_assert(sizeof(Lds) <= 160 * 1024, "window kernel LDS exceeds a CU's 160 KB");
 
@@ -292,12 +299,13 @@ __device__ __forceinline__ void store_pair(Lds& S, int w, const f32x4& v0, const
 // the layer-1 operand X and the wave's hidden-2 activations h2: dz2 of its features, given
 // to the other waves through LDS; dz1 = (W2^T q(dz2)) (1 - h1^2) of its hidden-1 features
 // (h1 recomputed from X); its partial of the input gradient W1^T q(dz1), and the sum of the
-// four waves' partials in wave order, gxo (inputs 0..11 of environment r).  With H.on it
+// four waves' partials in wave order, gxo (inputs c, 3 + c, 6 + c, 9 + c of environment lane / 4,
+// c = min(lane mod 4, 2)).  With H.on it
 // also stores the weight-gradient operands of its features.  w2t: the wave's 32 W2^T
 // fragments [M-tile m][K step s].
 __device__ __forceinline__ void mlp_backward(const OwnB& O, const bf16x8* w2t, const bf16x8& X, const bf16x8& GY,
                                              const f32x4 h2[4], int w, int lane, Lds& S, const HalfOut& H,
-                                             float gxo[12]) {
+                                             float gxo[4]) {
   const int g = lane >> 4, r = lane & 15;
   // hidden 2 (this wave's features): dz2 = (W3^T q(gy)) (1 - h2^2)
   f32x4 d[4];
@@ -346,11 +354,12 @@ __device__ __forceinline__ void mlp_backward(const OwnB& O, const bf16x8* w2t, c
   gx = mfma(O.w1t[1], pack8(e[2], e[3]), gx);
   *reinterpret_cast<f32x4*>(&S.GX[w][r][4 * g]) = gx;
   wg_sync();
+  const int slot = lane >> 2, c = min(lane & 3, 2);
 #pragma unroll
-  for (int j = 0; j < 12; ++j) {
-    float s = S.GX[0][r][j];
+  for (int j = 0; j < 4; ++j) {
+    float s = S.GX[0][slot][3 * j + c];
 #pragma unroll
-    for (int v = 1; v < WAVES; ++v) s += S.GX[v][r][j];
+    for (int v = 1; v < WAVES; ++v) s += S.GX[v][slot][3 * j + c];
     gxo[j] = s;
   }
 }
@@ -364,37 +373,30 @@ __device__ __forceinline__ void fill_w(Lds& S, const NetF& N, int first, int w, 
 }
 
 // ---------------------------------------------------------- lane <-> fragment moves ----
-// The 12 inputs (bf16) of environment `lane` into row `lane` of wave w's S.X (rows 12..31
-// zero); lanes 0..15 write.
-__device__ __forceinline__ void put_inputs(Lds& S, int w, int lane, const float o[12]) {
-  if (lane >= EPG) return;
-  bf16x8 a, b, z;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    a[j] = (__bf16)o[j];
-    b[j] = (__bf16)(j < 4 ? o[8 + j] : 0.0f);
-    z[j] = (__bf16)0.0f;
-  }
-  bf16x8* row = reinterpret_cast<bf16x8*>(&S.X[w][lane][0]);
-  row[0] = a;
-  row[1] = b;
-  row[2] = z;
-  row[3] = z;
+// The 12 inputs (bf16) of the wave's 16 environments into its S.X, lanes c < 3 of each quad
+// writing inputs c, 3 + c, 6 + c, 9 + c (the others were zeroed at the start).
+__device__ __forceinline__ void put_inputs(Lds& S, int w, int lane, float dpb, float rv, float v, float om) {
+  const int slot = lane >> 2, c = lane & 3;
+  if (c == 3) return;
+  __bf16* x = &S.X[w][slot][c];
+  x[0] = (__bf16)dpb;
+  x[3] = (__bf16)rv;
+  x[6] = (__bf16)v;
+  x[9] = (__bf16)om;
 }
 
 __device__ __forceinline__ bf16x8 input_frag(const Lds& S, int w, int lane) {
   const int g = lane >> 4, r = lane & 15;
-  return join2(*reinterpret_cast<const u32x2*>(&S.X[w][r][4 * g]),
-               *reinterpret_cast<const u32x2*>(&S.X[w][r][16 + 4 * g]));
+  return join2(*reinterpret_cast<const u32x2*>(&S.X[w][r][4 * g]), u32x2{0u, 0u});
 }
 
-// q(dL/dy) of environment `lane` (rows >= 6 zero) into wave w's S.G; lanes 0..15 write.
-__device__ __forceinline__ void put_gy(Lds& S, int w, int lane, const float gy[8]) {
-  if (lane >= EPG) return;
-  bf16x8 v;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) v[j] = (__bf16)gy[j];
-  *reinterpret_cast<bf16x8*>(&S.G[w][lane][0]) = v;
+// q(dL/dy) of the wave's 16 environments into its S.G: lanes c < 3 of each quad write rows c and
+// 3 + c (rows 6, 7 were zeroed at the start).
+__device__ __forceinline__ void put_gy(Lds& S, int w, int lane, float g0, float g1) {
+  const int slot = lane >> 2, c = lane & 3;
+  if (c == 3) return;
+  S.G[w][slot][c] = (__bf16)g0;
+  S.G[w][slot][3 + c] = (__bf16)g1;
 }
 
 __device__ __forceinline__ bf16x8 gy_frag(const Lds& S, int w, int lane) {
@@ -411,127 +413,51 @@ __device__ __forceinline__ float out_sum(const Lds& S, int b, int r, int j) {
   return s;
 }
 
-// Half fragments of wave 0's layer-1 inputs (feature tiles 0, 1) and of q(gy) (one tile).
+// Half fragments of wave 0's layer-1 inputs (one feature tile: inputs 16.. are zero) and of
+// q(gy) (one tile).
 __device__ __forceinline__ void store_input_halves(const Lds& S, int lane, u32x2* xh, u32x2* gh, size_t tile) {
   const int g = lane >> 4, r = lane & 15;
   bf16x4 v;
 #pragma unroll
-  for (int ft = 0; ft < 2; ++ft) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) v[s] = S.X[0][4 * g + s][16 * ft + r];
-    xh[(tile * 2 + ft) * 64 + lane] = __builtin_bit_cast(u32x2, v);
-  }
+  for (int s = 0; s < 4; ++s) v[s] = S.X[0][4 * g + s][r];
+  xh[tile * 64 + lane] = __builtin_bit_cast(u32x2, v);
 #pragma unroll
   for (int s = 0; s < 4; ++s) v[s] = r < 8 ? S.G[0][4 * g + s][r & 7] : (__bf16)0.0f;
   gh[tile * 64 + lane] = __builtin_bit_cast(u32x2, v);
 }
 
 // ------------------------------------------------------------------ environment --------
-__device__ __forceinline__ adj::Model<float> model_of(const VehArgs& V, const Params& P) {
+// This lane's model constants (component c of each triple, zero in lane 3): no current, weight
+// gamma W (gamma in parameter row 13), buoyancy centre at the centre of gravity.
+__device__ __forceinline__ qadj::QM<float> model_of(const VehArgs& V, const Params& P, const quad::QK& Q) {
   Model S;
   make_model(V, P, S);
-  adj::Model<float> M;
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    M.Mlin[i] = S.Mlin[i];
-    M.Mang[i] = S.Mang[i];
-    M.iMlin[i] = S.iMlin[i];
-    M.iMang[i] = S.iMang[i];
-    M.A1[i] = S.A1[i];
-  }
-#pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    M.DL[i] = S.DL[i];
-    M.DQ[i] = S.DQ[i];
-  }
-  M.BmW = __builtin_fmaf(-P.amp[0], V.W, V.B);   // B - gamma W (gamma in parameter row 13)
+  auto at = [&](const float* x) { return quad::pick(Q, x[0], x[1], x[2], 0.0f); };
+  qadj::QM<float> M;
+  M.Ml = at(S.Mlin);
+  M.iMl = at(S.iMlin);
+  M.Ma = at(S.Mang);
+  M.iMa = at(S.iMang);
+  M.A1 = at(S.A1);
+  M.DLi = at(S.DL) * M.iMl;
+  M.DQi = at(S.DQ) * M.iMl;
+  M.BmWi = __builtin_fmaf(-P.amp[0], V.W, V.B) * M.iMl;
+  M.DLa = at(S.DL + 3);
+  M.DQa = at(S.DQ + 3);
+  qadj::derive(M);
   return M;
 }
 
-__device__ __forceinline__ adj::Task<float> task_of(const TaskArgs& T) {
-  return adj::Task<float>{T.f_max, T.tau_max, T.w_pos, {T.d_pos[0], T.d_pos[1], T.d_pos[2]},
-                          T.w_att, T.w_act,   T.w_vel, T.w_mavg,
-                          T.beta};
-}
-
-// Noise of the sampled actions at one step: action c and 3 + c take the Box-Muller pair of
-// words (2c, 2c + 1) of counter (global id, step, 2, block).
-__device__ __forceinline__ void paper_noise(const EnvArgs& E, uint32_t gid, uint32_t step, float eps[6]) {
-  const U4 b0 = philox(U4{gid, step, 2u, 0u}, E.key0, E.key1);
-  const U4 b1 = philox(U4{gid, step, 2u, 1u}, E.key0, E.key1);
-  const uint32_t w0[3] = {b0.x, b0.z, b1.x}, w1[3] = {b0.y, b0.w, b1.y};
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const float rad = sqrtf(-2.0f * logf(u01_open0(w0[c])));
-    float sn, cs;
-    sincos_turns(u01(w1[c]), &sn, &cs);
-    eps[c] = rad * cs;
-    eps[3 + c] = rad * sn;
-  }
-}
-
-__device__ __forceinline__ void ck_store(float* ck, size_t Np, int t, int i, const adj::X13<float>& x, const float ab[6]) {
-  float* c = ck + (size_t)t * CK * Np + i;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    c[k * Np] = x.p[k];
-    c[(7 + k) * Np] = x.v[k];
-    c[(10 + k) * Np] = x.w[k];
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) c[(3 + k) * Np] = x.q[k];
-#pragma unroll
-  for (int k = 0; k < 6; ++k) c[(13 + k) * Np] = ab[k];
-}
-
-// Start state of RK4 substep s (1 .. substeps - 1) of step t: [t][s - 1][13 rows][Np].
-__device__ __forceinline__ void sub_store(float* sub, size_t Np, int t, int s, int i, const adj::X13<float>& x) {
-  float* c = sub + ((size_t)t * (MAX_S - 1) + (s - 1)) * 13 * Np + i;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    c[k * Np] = x.p[k];
-    c[(7 + k) * Np] = x.v[k];
-    c[(10 + k) * Np] = x.w[k];
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) c[(3 + k) * Np] = x.q[k];
-}
-
-// 13 state rows at stride Np from c.
-__device__ __forceinline__ void state_load(const float* c, size_t Np, adj::X13<float>& x) {
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    x.p[k] = c[k * Np];
-    x.v[k] = c[(7 + k) * Np];
-    x.w[k] = c[(10 + k) * Np];
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) x.q[k] = c[(3 + k) * Np];
-}
-
-// The state part of checkpoint t.
-__device__ __forceinline__ void ck_load_state(const float* ck, size_t Np, int t, int i, adj::X13<float>& x) {
-  state_load(ck + (size_t)t * CK * Np + i, Np, x);
-}
-
-// Start state of RK4 substep s of step t: checkpoint t for s = 0, else the stored substep
-// start state (the same row order and stride).
-__device__ __forceinline__ void start_load(const WinArgs& A, size_t Np, int t, int s, int i, adj::X13<float>& x) {
-  state_load(s == 0 ? A.ck + (size_t)t * CK * Np + i : A.sub + ((size_t)t * (MAX_S - 1) + (s - 1)) * 13 * Np + i, Np, x);
-}
-
-__device__ __forceinline__ void ck_load(const float* ck, size_t Np, int t, int i, adj::X13<float>& x, float ab[6]) {
-  const float* c = ck + (size_t)t * CK * Np + i;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    x.p[k] = c[k * Np];
-    x.v[k] = c[(7 + k) * Np];
-    x.w[k] = c[(10 + k) * Np];
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) x.q[k] = c[(3 + k) * Np];
-#pragma unroll
-  for (int k = 0; k < 6; ++k) ab[k] = c[(13 + k) * Np];
+// Noise of the sampled actions c and 3 + c at one step: the Box-Muller pair of words
+// (2c, 2c + 1) of counter (global id, step, 2, block); zero in lane 3.
+__device__ __forceinline__ void paper_noise(const EnvArgs& E, uint32_t gid, uint32_t step, int c, float& e0, float& e1) {
+  const U4 b = philox(U4{gid, step, 2u, (uint32_t)(c >> 1)}, E.key0, E.key1);
+  const uint32_t w0 = (c & 1) ? b.z : b.x, w1 = (c & 1) ? b.w : b.y;
+  const float rad = sqrtf(-2.0f * logf(u01_open0(w0)));
+  float sn, cs;
+  sincos_turns(u01(w1), &sn, &cs);
+  e0 = c < 3 ? rad * cs : 0.0f;
+  e1 = c < 3 ? rad * sn : 0.0f;
 }
 
 // ------------------------------------------------------------------ window kernel ------
@@ -540,46 +466,58 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
   __shared__ Lds S;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int g = lane >> 4, r = lane & 15;
-  const int i = blockIdx.x * EPG + r;
+  const int g = lane >> 4, r = lane & 15;      // lane of the MFMA layouts
+  const int slot = lane >> 2, c = lane & 3;    // lane of the four-lane physics
+  const quad::QK Q = quad::make_qk(lane);
+  const qadj::LaneK<float> K{Q.m3, 1.0f - Q.m3, Q.e1, Q.e2, Q.d2};
+  const int i = blockIdx.x * EPG + slot;
   const int N = E.n;
   const bool valid = i < N;
-  const bool lead = threadIdx.x < EPG;   // the lanes that write the per-environment results
-  const int ic = valid ? i : N - 1;      // idle slots step a copy of the last environment
+  const int ic = valid ? i : N - 1;            // idle slots step a copy of the last environment
   const size_t Nz = (size_t)N, Np = (size_t)A.Np;
   const int h = A.steps;
   const uint32_t gid = E.env_offset + (uint32_t)i;
+  // wave 0 writes the state's results, wave 1 the recorded observations, wave 2 the actions and
+  // their gradients, wave 3 rewards and done flags (every wave holds all of them)
+  const bool w_obs = w == 1 && valid && A.o_obs, w_act = w == 2 && valid && A.o_act;
+  const bool w_gact = w == 2 && valid && A.o_gact, w_rew = w == 3 && valid && c == 0;
 
-  adj::X13<float> x;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    x.p[k] = E.state[k * Nz + ic];
-    x.v[k] = E.state[(7 + k) * Nz + ic];
-    x.w[k] = E.state[(10 + k) * Nz + ic];
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) x.q[k] = E.state[(3 + k) * Nz + ic];
+  if (threadIdx.x <= MAX_H) S.pw[threadIdx.x] = powf(A.gamma, (float)threadIdx.x);
+  for (int k = threadIdx.x; k < WAVES * EPG * 16; k += 64 * WAVES) (&S.X[0][0][0])[k] = (__bf16)0.0f;
+  for (int k = threadIdx.x; k < WAVES * EPG * 8; k += 64 * WAVES) (&S.G[0][0][0])[k] = (__bf16)0.0f;
+  wg_sync();
+
+  // environment of this quad: row k of a 3-vector in lanes c < 3, zero in lane 3
+  auto row3 = [&](const float* p, int k) { return c < 3 ? p[(size_t)(k + min(c, 2)) * Nz + ic] : 0.0f; };
+  float p = row3(E.state, 0);
+  qadj::QX<float> x{E.state[(size_t)(c < 3 ? 4 + c : 3) * Nz + ic], row3(E.state, 7), row3(E.state, 10)};
   Params P;
   load_params(E.params, N, ic, P);
-  const adj::Model<float> M = model_of(V, P);
-  const adj::Task<float> K = task_of(E.tk);
-  float pg[3] = {P.pg[0], P.pg[1], P.pg[2]}, qg[4] = {P.qg[0], P.qg[1], P.qg[2], P.qg[3]};
-  int ep = E.ep_step[ic];
-  uint32_t episode = E.episode[ic];
-  float ab[6];
-#pragma unroll
-  for (int j = 0; j < 6; ++j) ab[j] = E.obs[(12 + j) * Nz + ic];
+  const qadj::QM<float> M = model_of(V, P, Q);
+  const float pg = quad::pick(Q, P.pg[0], P.pg[1], P.pg[2], 0.0f);
+  const float qg = quad::pick(Q, P.qg[1], P.qg[2], P.qg[3], P.qg[0]);
+  const int ep = E.ep_step[ic];
+  const uint32_t episode = E.episode[ic];
+  float ab0 = row3(E.obs, 12), ab1 = row3(E.obs, 15);
   const bool ends = ep + h == E.H;
-  float sig[6], b3[6];
-#pragma unroll
-  for (int j = 0; j < 6; ++j) {
-    sig[j] = MODE == MODE_SAMPLE ? expf(A.log_std[j]) : 0.0f;
-    b3[j] = MODE != MODE_EXTERNAL ? A.pol.b[2 * HID + j] : 0.0f;
+  const TaskArgs& tk = E.tk;
+  const float dc = quad::pick(Q, tk.d_pos[0], tk.d_pos[1], tk.d_pos[2], 0.0f);
+  float sig0 = 0.0f, sig1 = 0.0f, b30 = 0.0f, b31 = 0.0f;
+  if (c < 3) {
+    if (MODE == MODE_SAMPLE) {
+      sig0 = expf(A.log_std[c]);
+      sig1 = expf(A.log_std[3 + c]);
+    }
+    if (MODE != MODE_EXTERNAL) {
+      b30 = A.pol.b[2 * HID + c];
+      b31 = A.pol.b[2 * HID + 3 + c];
+    }
   }
-  // this wave's hidden-2 activations of step t
-  auto h2_at = [&](int t) {
-    return A.h2s + (((size_t)t * gridDim.x + blockIdx.x) * WAVES + w) * H2_F4 + lane;
-  };
+  // where this workgroup's lanes keep the forward sweep's records
+  const size_t G = gridDim.x, at0 = (size_t)blockIdx.x * 64 + lane;
+  auto rec_at = [&](int t, int s, int stage) { return A.rec + (((size_t)t * E.substeps + s) * 4 + stage) * G * 64 + at0; };
+  auto row_at = [&](f32x4* a, int t) { return a + (size_t)t * G * 64 + at0; };
+  auto h2_at = [&](int t) { return A.h2s + (((size_t)t * G + blockIdx.x) * WAVES + w) * H2_F4 + lane; };
 
   // ---------------------------------------------------------------- forward sweep
   OwnF of{};
@@ -588,16 +526,15 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
     of = own_fwd(A.pol, w, lane);
   }
   float Jr = 0.0f;
+  qadj::QObsK<float> o = qadj::observe(K, p, x.q, pg, qg);
   for (int t = 0; t < h; ++t) {
-    if (lead) ck_store(A.ck, Np, t, i, x, ab);
-    float o[12], a[6];
-    adj::observe(x, pg, qg, o);
+    float a0, a1;
     if (MODE == MODE_EXTERNAL) {
-#pragma unroll
-      for (int j = 0; j < 6; ++j) a[j] = A.ext[((size_t)j * h + t) * Nz + ic];
+      a0 = c < 3 ? A.ext[((size_t)c * h + t) * Nz + ic] : 0.0f;
+      a1 = c < 3 ? A.ext[((size_t)(3 + c) * h + t) * Nz + ic] : 0.0f;
     } else {
       lds_sync();
-      put_inputs(S, w, lane, o);
+      put_inputs(S, w, lane, o.dpb, o.rv, x.v, x.w);
       lds_sync();
       const bf16x8 X = input_frag(S, w, lane);
       f32x4 h2[4];
@@ -608,64 +545,72 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
       const int b = t & 1;
       if (g < 2) *reinterpret_cast<f32x4*>(&S.Y[b][w][r][4 * g]) = y;
       wg_sync();
-#pragma unroll
-      for (int j = 0; j < 6; ++j) a[j] = out_sum(S, b, r, j) + b3[j];
+      a0 = c < 3 ? out_sum(S, b, slot, min(c, 2)) + b30 : 0.0f;
+      a1 = c < 3 ? out_sum(S, b, slot, 3 + min(c, 2)) + b31 : 0.0f;
       if (MODE == MODE_SAMPLE) {
-        float eps[6];
-        paper_noise(E, gid, A.step0 + (uint32_t)t, eps);
-#pragma unroll
-        for (int j = 0; j < 6; ++j) a[j] = __builtin_fmaf(sig[j], eps[j], a[j]);
+        float e0, e1;
+        paper_noise(E, gid, A.step0 + (uint32_t)t, c, e0, e1);
+        a0 = __builtin_fmaf(sig0, e0, a0);
+        a1 = __builtin_fmaf(sig1, e1, a1);
       }
     }
-    if (lead)
-#pragma unroll
-      for (int j = 0; j < 6; ++j) A.acts[((size_t)t * 6 + j) * Np + i] = a[j];
-    if (lead && valid) {
-      const size_t at = (size_t)t * Nz + i, rs = (size_t)h * Nz;
-      if (A.o_obs)
-#pragma unroll
-        for (int k = 0; k < 23; ++k) A.o_obs[k * rs + at] = k < 12 ? o[k] : 0.0f;
-      if (A.o_act)
-#pragma unroll
-        for (int k = 0; k < 8; ++k) A.o_act[k * rs + at] = k < 6 ? a[k] : 0.0f;
+    if (w == 0) {
+      *row_at(A.aa, t) = f32x4{a0, a1, ab0, ab1};
+    } else if (w == 1) {
+      *row_at(A.obk, t) = f32x4{o.dpb, o.rv, o.sk, o.kn};
     }
-    float u[6], tau[6];
+    const size_t at = (size_t)t * Nz + i, rs = (size_t)h * Nz;
+    if (w_obs) {
+      if (c < 3) {
+        A.o_obs[c * rs + at] = o.dpb;
+        A.o_obs[(3 + c) * rs + at] = o.rv;
+        A.o_obs[(6 + c) * rs + at] = x.v;
+        A.o_obs[(9 + c) * rs + at] = x.w;
+      }
 #pragma unroll
-    for (int j = 0; j < 6; ++j) u[j] = fminf(fmaxf(a[j], -1.0f), 1.0f);
-    adj::wrench(K, u, tau);
+      for (int k = 12; k < 24; k += 4)
+        if (k + c < 23) A.o_obs[(k + c) * rs + at] = 0.0f;
+    }
+    if (w_act) {
+      if (c < 3) {
+        A.o_act[c * rs + at] = a0;
+        A.o_act[(3 + c) * rs + at] = a1;
+      } else {
+        A.o_act[6 * rs + at] = 0.0f;
+        A.o_act[7 * rs + at] = 0.0f;
+      }
+    }
+    const float u0 = fminf(fmaxf(a0, -1.0f), 1.0f), u1 = fminf(fmaxf(a1, -1.0f), 1.0f);
+    const float tfi = tk.f_max * u0 * M.iMl, tm = tk.tau_max * u1;
     for (int s = 0; s < E.substeps; ++s) {
-      if (s > 0 && lead) sub_store(A.sub, Np, t, s, i, x);
-      adj::substep(M, tau, E.h, x);
+      qadj::QX<float> st[4];
+      float inv;
+      const float p0 = p;
+      qadj::substep(K, M, tfi, tm, E.h, p, x, st, inv);
+      // wave w stores stage w's input
+      const qadj::QX<float> mine = w == 0 ? st[0] : (w == 1 ? st[1] : (w == 2 ? st[2] : st[3]));
+      *rec_at(t, s, w) = f32x4{mine.q, mine.v, mine.w, w == 0 ? p0 : inv};
     }
-    float o1[12];
-    adj::observe(x, pg, qg, o1);
-    const float rw = adj::reward(K, o1, u, ab);
-#pragma unroll
-    for (int j = 0; j < 6; ++j) ab[j] = __builtin_fmaf(K.beta, ab[j], (1.0f - K.beta) * u[j]);
-    Jr = __builtin_fmaf(powf(A.gamma, (float)t), rw, Jr);
-    if (lead && valid) {
-      if (A.o_reward) A.o_reward[(size_t)t * Nz + i] = rw;
-      if (A.o_done) A.o_done[(size_t)t * Nz + i] = (t == h - 1 && ends) ? 1.0f : 0.0f;
+    o = qadj::observe(K, p, x.q, pg, qg);
+    const quad::QObs ob{o.dpb, o.rv, 0.0f};
+    const float rw = quad::paper_reward(tk, dc, ob, x.w, u0, u1, ab0, ab1);
+    ab0 = __builtin_fmaf(tk.beta, ab0, (1.0f - tk.beta) * u0);
+    ab1 = __builtin_fmaf(tk.beta, ab1, (1.0f - tk.beta) * u1);
+    Jr = __builtin_fmaf(S.pw[t], rw, Jr);
+    if (w_rew) {
+      if (A.o_reward) A.o_reward[at] = rw;
+      if (A.o_done) A.o_done[at] = (t == h - 1 && ends) ? 1.0f : 0.0f;
     }
   }
-  if (lead) ck_store(A.ck, Np, h, i, x, ab);   // the final state, before any reset
-  __syncthreads();   // wave 0's checkpoints and actions are read by every wave in the reverse sweep
+  __syncthreads();   // the waves' records are read by every wave in the reverse sweep
 
   // ------------------------------------------------ terminal value, its input gradient
-  float oh[12];
-  adj::observe(x, pg, qg, oh);
-  float go_h[12];
-#pragma unroll
-  for (int k = 0; k < 12; ++k) go_h[k] = 0.0f;
+  float go[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // cotangents of dpb, rotation vector, v, omega
   float vlast = 0.0f;
   if (A.has_val) {
-    float gy[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) gy[j] = 0.0f;
-    gy[0] = valid ? -powf(A.gamma, (float)h) * A.inv_nh : 0.0f;
     lds_sync();
-    put_inputs(S, w, lane, oh);
-    put_gy(S, w, lane, gy);
+    put_inputs(S, w, lane, o.dpb, o.rv, x.v, x.w);
+    put_gy(S, w, lane, (valid && c == 0) ? -S.pw[h] * A.inv_nh : 0.0f, 0.0f);
     lds_sync();
     const bf16x8 X = input_frag(S, w, lane), GY = gy_frag(S, w, lane);
     f32x4 h2[4];
@@ -673,61 +618,46 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
     const int b = h & 1;
     if (g < 2) *reinterpret_cast<f32x4*>(&S.Y[b][w][r][4 * g]) = y;
     wg_sync();
-    vlast = out_sum(S, b, r, 0) + A.val.b[2 * HID];
+    vlast = out_sum(S, b, slot, 0) + A.val.b[2 * HID];
     const HalfOut off{nullptr, nullptr, nullptr, nullptr, 0, false};
-    mlp_backward(own_bwd(A.val, w, lane), A.val.f + (size_t)(F_W2T + WF * w) * 64, X, GY, h2, w, lane, S, off, go_h);
+    mlp_backward(own_bwd(A.val, w, lane), A.val.f + (size_t)(F_W2T + WF * w) * 64, X, GY, h2, w, lane, S, off, go);
   }
 
   // ------------------------------------------- environment update (reset at the episode end)
-  if (lead && valid) {
-    uint32_t nf = 0;   // non-finite components of the window's end state, before any reset
-#pragma unroll
-    for (int k = 0; k < 3; ++k) nf += nonfinite(x.p[k]) + nonfinite(x.v[k]) + nonfinite(x.w[k]);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) nf += nonfinite(x.q[k]);
-    report_status(E.status, nf, 0u);
-    adj::X13<float> xn = x;
-    float abn[6], on[12];
-#pragma unroll
-    for (int j = 0; j < 6; ++j) abn[j] = ab[j];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) on[k] = oh[k];
-    int epn = ep + h;
-    uint32_t epi = episode;
+  if (w == 0 && valid) {
+    quad::QEnv X;
+    X.p = p;
+    X.q = x.q;
+    X.v = x.v;
+    X.om = x.w;
+    X.u0 = ab0;
+    X.u1 = ab1;
+    X.ep = ep + h;
+    X.episode = episode;
+    X.ob = quad::QObs{o.dpb, o.rv, 0.0f};
+    // non-finite components of the window's end state, before any reset
+    report_status(E.status, quad::nonfinite_quad(c, X), 0u);
     if (ends) {
-      epi += 1u;
-      State xs;
-      Params Pn;
-      paper_reset_draws(E, gid, epi, xs, Pn);
-      store_params(E.params, N, i, Pn);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        xn.p[k] = xs.p[k];
-        xn.v[k] = xs.v[k];
-        xn.w[k] = xs.w[k];
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) xn.q[k] = xs.q[k];
-#pragma unroll
-      for (int j = 0; j < 6; ++j) abn[j] = 0.0f;
-      epn = 0;
-      adj::observe(xn, Pn.pg, Pn.qg, on);
+      quad::QModel Mn;
+      quad::QRef Fn;
+      quad::QRefCols rc;
+      float prn, qrn, dist;
+      quad::new_episode<true>(V, E, Q, gid, i, true, X, Mn, Fn, prn, qrn, rc, dist);
     }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      E.state[k * Nz + i] = xn.p[k];
-      E.state[(7 + k) * Nz + i] = xn.v[k];
-      E.state[(10 + k) * Nz + i] = xn.w[k];
+    quad::store_state(E.state, Nz, (size_t)i, c, X);
+    if (c < 3) {
+      E.obs[c * Nz + i] = X.ob.dpb;
+      E.obs[(3 + c) * Nz + i] = X.ob.c0;
+      E.obs[(6 + c) * Nz + i] = X.v;
+      E.obs[(9 + c) * Nz + i] = X.om;
+      E.obs[(12 + c) * Nz + i] = X.u0;
+      E.obs[(15 + c) * Nz + i] = X.u1;
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) E.state[(3 + k) * Nz + i] = xn.q[k];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) E.obs[k * Nz + i] = on[k];
-#pragma unroll
-    for (int j = 0; j < 6; ++j) E.obs[(12 + j) * Nz + i] = abn[j];
-    E.ep_step[i] = epn;
-    E.episode[i] = epi;
-    if (A.o_vlast) A.o_vlast[i] = vlast;
+    if (c == 0) {
+      E.ep_step[i] = X.ep;
+      E.episode[i] = X.episode;
+      if (A.o_vlast) A.o_vlast[i] = vlast;
+    }
   }
 
   // ---------------------------------------------------------------- reverse sweep
@@ -736,10 +666,29 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
     fill_w(S, A.pol, F_W2T + WF * w, w, lane);
     ob = own_bwd(A.pol, w, lane);
   }
-  adj::X13<float> lam;
-  adj::zero(lam);
-  adj::observe_vjp(x, pg, qg, go_h, lam);
-  float lab[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f}, gls[6] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  float lp = 0.0f;
+  qadj::QX<float> l{0.0f, 0.0f, 0.0f};
+  // Cotangents of the observation at one point of the trajectory, the network's in go, those of
+  // the reward r_t that it enters added (weight -gamma^t / (N h)), through the observation.
+  auto through_obs = [&](int t, float cr, const qadj::QObsK<float>& ok, float pp, const qadj::QX<float>& xx) {
+    if (t >= 0) {
+      go[0] -= 2.0f * cr * tk.w_pos * dc * dc * ok.dpb;
+      go[1] -= 2.0f * cr * tk.w_att * ok.rv;
+      go[3] -= 2.0f * cr * tk.w_vel * xx.w;
+    }
+    go[0] *= K.m3;
+    go[1] *= K.m3;
+    qadj::observe_vjp(K, pp, xx.q, pg, qg, ok.sk, ok.kn, go[0], go[1], lp, l.q);
+    l.v += K.m3 * go[2];
+    l.w += K.m3 * go[3];
+  };
+  float cr = valid ? -S.pw[h - 1] * A.inv_nh : 0.0f;   // weight of the reward r_t being taken backward
+  through_obs(h - 1, cr, o, p, x);
+  float qn = x.q;                                        // the quaternion at the end of the substep
+  float la0 = 0.0f, la1 = 0.0f, gls0 = 0.0f, gls1 = 0.0f;
+  f32x4 rs[4];                                           // the substep's stage records, loaded one substep ahead
+#pragma unroll
+  for (int k = 0; k < 4; ++k) rs[k] = *rec_at(h - 1, E.substeps - 1, k);
   for (int t = h - 1; t >= 0; --t) {
     f32x4 h2[4];
     if (MODE != MODE_EXTERNAL) {   // issued first: the loads complete during the state adjoint
@@ -747,95 +696,87 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
 #pragma unroll
       for (int m = 0; m < 4; ++m) h2[m] = hs[m * 64];
     }
-    // the step's start and end states (checkpoints t and t + 1) as the forward computed them
-    adj::X13<float> x0, x1;
-    float abt[6], a[6], u[6], tau[6];
-    ck_load(A.ck, Np, t, i, x0, abt);
-    ck_load_state(A.ck, Np, t + 1, i, x1);
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      a[j] = A.acts[((size_t)t * 6 + j) * Np + i];
-      u[j] = fminf(fmaxf(a[j], -1.0f), 1.0f);
-    }
-    adj::wrench(K, u, tau);
-    // reward r_t(o(s_{t+1}), u_t, abar_t) with weight -gamma^t / (N h)
-    const float cr = valid ? -powf(A.gamma, (float)t) * A.inv_nh : 0.0f;
-    float o1[12], go[12], gu[6] = {0, 0, 0, 0, 0, 0}, gab[6] = {0, 0, 0, 0, 0, 0};
-    adj::observe(x1, pg, qg, o1);
-    adj::reward_grad(K, cr, o1, u, abt, go, gu, gab);
-    adj::observe_vjp(x1, pg, qg, go, lam);
-    // abar_{t+1} = beta abar_t + (1 - beta) u_t
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-      gab[j] += K.beta * lab[j];
-      gu[j] += (1.0f - K.beta) * lab[j];
-    }
-    // RK4 substeps in reverse, each from its stored start state (loaded one substep ahead);
-    // one copy of the substep adjoint in the loop keeps the code within the instruction cache
-    float gtau[6] = {0, 0, 0, 0, 0, 0};
-    adj::X13<float> xs;
-    start_load(A, Np, t, E.substeps - 1, i, xs);
+    const f32x4 aa = *row_at(A.aa, t), okv = *row_at(A.obk, t);
+    const float u0 = fminf(fmaxf(aa.x, -1.0f), 1.0f), u1 = fminf(fmaxf(aa.y, -1.0f), 1.0f);
+    // RK4 substeps in reverse; one copy of the adjoint in the loop keeps the code within the
+    // instruction cache
+    float gtf = 0.0f, gtm = 0.0f, pt = 0.0f;
+    qadj::QX<float> x0{};
 #pragma unroll 1
     for (int s = E.substeps - 1; s >= 0; --s) {
-      adj::X13<float> xn;
-      start_load(A, Np, t, s > 0 ? s - 1 : 0, i, xn);
-      adj::substep_vjp(M, tau, E.h, xs, lam, gtau);
-      xs = xn;
-    }
+      f32x4 nx[4];
+      const int tn = s > 0 ? t : max(t - 1, 0), sn = s > 0 ? s - 1 : (t > 0 ? E.substeps - 1 : 0);
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      gu[j] += K.f_max * gtau[j];
-      gu[3 + j] += K.tau_max * gtau[3 + j];
+      for (int k = 0; k < 4; ++k) nx[k] = *rec_at(tn, sn, k);
+      qadj::QX<float> st[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) st[k] = qadj::QX<float>{rs[k].x, rs[k].y, rs[k].z};
+      qadj::substep_vjp(K, M, E.h, st, rs[3].w, qn, lp, l, gtf, gtm);
+      qn = st[0].q;
+      x0 = st[0];
+      pt = rs[0].w;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) rs[k] = nx[k];
     }
+    // reward terms of the action and abar_{t+1} = beta abar_t + (1 - beta) u_t
+    const float m0 = 2.0f * cr * tk.w_mavg * (u0 - aa.z), m1 = 2.0f * cr * tk.w_mavg * (u1 - aa.w);
+    const float gu0 = (1.0f - tk.beta) * la0 - m0 + tk.f_max * gtf;
+    const float gu1 = (1.0f - tk.beta) * la1 - m1 - 2.0f * cr * tk.w_act * u1 + tk.tau_max * gtm;
+    la0 = __builtin_fmaf(tk.beta, la0, m0);
+    la1 = __builtin_fmaf(tk.beta, la1, m1);
     // clip: the derivative passes on [-1, 1]
-    float ga[8];
-#pragma unroll
-    for (int j = 0; j < 6; ++j) ga[j] = (a[j] >= -1.0f && a[j] <= 1.0f) ? gu[j] : 0.0f;
-    ga[6] = ga[7] = 0.0f;
-    if (lead && valid && A.o_gact)
-#pragma unroll
-      for (int k = 0; k < 8; ++k) A.o_gact[((size_t)k * h + t) * Nz + i] = ga[k];
+    const float ga0 = (c < 3 && aa.x >= -1.0f && aa.x <= 1.0f) ? gu0 : 0.0f;
+    const float ga1 = (c < 3 && aa.y >= -1.0f && aa.y <= 1.0f) ? gu1 : 0.0f;
+    if (w_gact) {
+      const size_t at = (size_t)t * Nz + i, rs_ = (size_t)h * Nz;
+      if (c < 3) {
+        A.o_gact[c * rs_ + at] = ga0;
+        A.o_gact[(3 + c) * rs_ + at] = ga1;
+      } else {
+        A.o_gact[6 * rs_ + at] = 0.0f;
+        A.o_gact[7 * rs_ + at] = 0.0f;
+      }
+    }
+    go[0] = go[1] = go[2] = go[3] = 0.0f;
+    const qadj::QObsK<float> ok{okv.x, okv.y, okv.z, okv.w};
     if (MODE != MODE_EXTERNAL) {
       if (MODE == MODE_SAMPLE) {
-        float eps[6];
-        paper_noise(E, gid, A.step0 + (uint32_t)t, eps);
-#pragma unroll
-        for (int j = 0; j < 6; ++j) gls[j] = __builtin_fmaf(ga[j] * sig[j], eps[j], gls[j]);
+        float e0, e1;
+        paper_noise(E, gid, A.step0 + (uint32_t)t, c, e0, e1);
+        gls0 = __builtin_fmaf(ga0 * sig0, e0, gls0);
+        gls1 = __builtin_fmaf(ga1 * sig1, e1, gls1);
       }
       // the policy's input gradient at o_t = o(s_t)
-      float ot[12];
-      adj::observe(x0, pg, qg, ot);
       lds_sync();
-      put_inputs(S, w, lane, ot);
-      put_gy(S, w, lane, ga);
+      put_inputs(S, w, lane, ok.dpb, ok.rv, x0.v, x0.w);
+      put_gy(S, w, lane, ga0, ga1);
       lds_sync();
       const bf16x8 X = input_frag(S, w, lane), GY = gy_frag(S, w, lane);
-      const size_t tile = (size_t)t * gridDim.x + blockIdx.x;
+      const size_t tile = (size_t)t * G + blockIdx.x;
       if (A.want_grad && w == 0) store_input_halves(S, lane, A.x_half, A.gy_half, tile);
       const HalfOut H{A.h1_half, A.h2_half, A.dz2_half, A.dz1_half, tile, A.want_grad != 0};
-      float gxo[12];
-      mlp_backward(ob, &S.W[w][0][0], X, GY, h2, w, lane, S, H, gxo);
-      adj::observe_vjp(x0, pg, qg, gxo, lam);
+      mlp_backward(ob, &S.W[w][0][0], X, GY, h2, w, lane, S, H, go);
     }
-#pragma unroll
-    for (int j = 0; j < 6; ++j) lab[j] = gab[j];
+    cr = (valid && t > 0) ? -S.pw[t > 0 ? t - 1 : 0] * A.inv_nh : 0.0f;
+    through_obs(t - 1, cr, ok, pt, x0);
   }
-  if (lead && valid && A.o_gs0) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      A.o_gs0[k * Nz + i] = lam.p[k];
-      A.o_gs0[(7 + k) * Nz + i] = lam.v[k];
-      A.o_gs0[(10 + k) * Nz + i] = lam.w[k];
+  if (w == 0 && valid && A.o_gs0) {
+    if (c < 3) {
+      A.o_gs0[c * Nz + i] = lp;
+      A.o_gs0[(7 + c) * Nz + i] = l.v;
+      A.o_gs0[(10 + c) * Nz + i] = l.w;
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) A.o_gs0[(3 + k) * Nz + i] = lam.q[k];
+    A.o_gs0[(size_t)(c < 3 ? 4 + c : 3) * Nz + i] = l.q;
   }
-  if (lead) {
-    A.J[i] = valid ? __builtin_fmaf(powf(A.gamma, (float)h), vlast, Jr) : 0.0f;
-    A.Jr[i] = valid ? Jr : 0.0f;
-    A.vl[i] = valid ? vlast : 0.0f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) A.gls[j * Np + i] = (valid && j < 6) ? gls[j] : 0.0f;
+  if (w == 0) {
+    if (c == 0) {
+      A.J[i] = valid ? __builtin_fmaf(S.pw[h], vlast, Jr) : 0.0f;
+      A.Jr[i] = valid ? Jr : 0.0f;
+      A.vl[i] = valid ? vlast : 0.0f;
+    }
+    // rows 6, 7: padding
+    A.gls[(size_t)(c < 3 ? c : 6) * Np + i] = (valid && c < 3) ? gls0 : 0.0f;
+    A.gls[(size_t)(c < 3 ? 3 + c : 7) * Np + i] = (valid && c < 3) ? gls1 : 0.0f;
   }
 }
 
@@ -859,24 +800,23 @@ __global__ __launch_bounds__(256) void k_wsmall(const u32x2* __restrict__ x_half
   const int g = lane >> 4, r = lane & 15;
   const int per = (steps + gridDim.x - 1) / gridDim.x;
   const int u0 = blockIdx.x * per, u1 = min(steps, u0 + per);
-  f32x4 w1[4][2], w3[4];
+  f32x4 w1[4], w3[4];
   float b1[4], b2[4], b3 = 0.0f;
 #pragma unroll
   for (int mt = 0; mt < 4; ++mt) {
-    w1[mt][0] = w1[mt][1] = w3[mt] = zero4();
+    w1[mt] = w3[mt] = zero4();
     b1[mt] = b2[mt] = 0.0f;
   }
   auto at = [&](int tile, int ft, int nft) { return ((size_t)tile * nft + ft) * 64 + lane; };
   // operands of one K step (sample tiles 2u, 2u + 1), loaded one K step ahead
   struct In {
-    u32x2 x[2][2], gy[2], d1[4][2], h2[4][2], d2[4][2];
+    u32x2 x[2], gy[2], d1[4][2], h2[4][2], d2[4][2];
   };
   auto load = [&](int u, In& v) {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       const int tl = 2 * u + k;
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) v.x[nt][k] = x_half[at(tl, nt, 2)];
+      v.x[k] = x_half[at(tl, 0, 1)];
       v.gy[k] = gy_half[at(tl, 0, 1)];
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) {
@@ -892,9 +832,7 @@ __global__ __launch_bounds__(256) void k_wsmall(const u32x2* __restrict__ x_half
   for (int u = u0; u < u1; ++u) {
     In nxt;
     load(min(u + 1, u1 - 1), nxt);   // unconditional (clamped), so no wait covers it early
-    bf16x8 xb[2];
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) xb[nt] = join2(cur.x[nt][0], cur.x[nt][1]);
+    const bf16x8 xb = join2(cur.x[0], cur.x[1]);
     const bf16x8 gb = join2(cur.gy[0], cur.gy[1]);
     if (w == 0) b3 += sum8(gb);
 #pragma unroll
@@ -902,8 +840,7 @@ __global__ __launch_bounds__(256) void k_wsmall(const u32x2* __restrict__ x_half
       const bf16x8 d1 = join2(cur.d1[mt][0], cur.d1[mt][1]);
       const bf16x8 h2 = join2(cur.h2[mt][0], cur.h2[mt][1]);
       const bf16x8 d2 = join2(cur.d2[mt][0], cur.d2[mt][1]);
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) w1[mt][nt] = mfma(d1, xb[nt], w1[mt][nt]);
+      w1[mt] = mfma(d1, xb, w1[mt]);
       w3[mt] = mfma(h2, gb, w3[mt]);
       b1[mt] += sum8(d1);
       b2[mt] += sum8(d2);
@@ -916,8 +853,8 @@ __global__ __launch_bounds__(256) void k_wsmall(const u32x2* __restrict__ x_half
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int k = 64 * w + 16 * mt + 4 * g + i;
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt) P.part_w1[((size_t)G * HID + k) * 32 + 16 * nt + r] = w1[mt][nt][i];
+      P.part_w1[((size_t)G * HID + k) * 32 + r] = w1[mt][i];
+      P.part_w1[((size_t)G * HID + k) * 32 + 16 + r] = 0.0f;   // inputs 16.. of the paper task are zero
       P.part_w3t[((size_t)G * HID + k) * 16 + r] = w3[mt][i];
     }
     // lanes (g, r), g = 0..3, hold partial sums of feature 16 (4w + mt) + r: add in g order
@@ -1024,18 +961,18 @@ inline size_t work_layout(int N, int h, size_t off[WORK_PARTS]) {
   const size_t Np = s.Np, tp = s.tiles_p, G = MAX_GROUPS, half = tp * 64 * 8;
   const size_t sizes[WORK_PARTS] = {
       2 * (size_t)F_END * 64 * 16,          // 0 fragments of the policy and the value net
-      (size_t)(h + 1) * CK * Np * 4,        // 1 checkpoints
-      (size_t)h * 6 * Np * 4,               // 2 actions
+      (size_t)h * (Np / EPG) * 64 * 16,   // 1 observations with their derivative factors
+      (size_t)h * (Np / EPG) * 64 * 16,     // 2 actions and action averages
       Np * 4, Np * 4, Np * 4,               // 3 J, 4 Jr, 5 V(o_h)
       8 * Np * 4,                           // 6 d log_std per environment
-      half * 2, half, half * 16, half * 16, half * 16, half * 16,   // 7 x, 8 gy, 9 h1, 10 h2, 11 dz2, 12 dz1
+      half, half, half * 16, half * 16, half * 16, half * 16,   // 7 x, 8 gy, 9 h1, 10 h2, 11 dz2, 12 dz1
       G * HID * 32 * 4, G * HID * 4,        // 13 part_w1, 14 part_b1
       G * HID * 16 * 4, G * HID * 4,        // 15 part_w3t, 16 part_b2
       G * 16 * 4 + G * 16 * 4,              // 17 part_b3 + part_ls
       G * HID * HID * 4,                    // 18 part_w2
       4096 * 4,                             // 19 per-block sums of squares
       (size_t)h * (Np / EPG) * WAVES * H2_F4 * 16,   // 20 policy hidden-2 activations
-      (size_t)h * (MAX_S - 1) * 13 * Np * 4};        // 21 RK4 substep start states
+      (size_t)h * MAX_S * 4 * (Np / EPG) * 64 * 16};   // 21 RK4 stage inputs
   size_t o = 0;
   for (int k = 0; k < WORK_PARTS; ++k) {
     off[k] = o;
@@ -1127,8 +1064,8 @@ int auv_shac_window(auv_env* env, const auv_shac_config* cfg, const auv_mlp* pol
   A.pol = NetF{frags, ext ? nullptr : policy->b, ACT};
   A.val = NetF{frags + F_END * 64, value ? value->b : nullptr, 1};
   A.log_std = (!ext && policy->log_std) ? policy->log_std : nullptr;
-  A.ck = (float*)at(1);
-  A.acts = (float*)at(2);
+  A.obk = (f32x4*)at(1);
+  A.aa = (f32x4*)at(2);
   A.J = (float*)at(3);
   A.Jr = (float*)at(4);
   A.vl = (float*)at(5);
@@ -1140,7 +1077,7 @@ int auv_shac_window(auv_env* env, const auv_shac_config* cfg, const auv_mlp* pol
   A.dz2_half = (u32x2*)at(11);
   A.dz1_half = (u32x2*)at(12);
   A.h2s = (f32x4*)at(20);
-  A.sub = (float*)at(21);
+  A.rec = (f32x4*)at(21);
   A.Np = sh.Np;
   if (out) {
     A.ext = out->actions;
@@ -1166,7 +1103,7 @@ int auv_shac_window(auv_env* env, const auv_shac_config* cfg, const auv_mlp* pol
     if (sh.tiles_p > sh.tiles) {
       const size_t pad = (size_t)(sh.tiles_p - sh.tiles) * 64 * 2;   // u32 per tile and feature tile
       const int parts[6] = {7, 8, 9, 10, 11, 12};
-      const int nft[6] = {2, 1, 16, 16, 16, 16};
+      const int nft[6] = {1, 1, 16, 16, 16, 16};
       for (int k = 0; k < 6; ++k) {
         uint32_t* p = (uint32_t*)at(parts[k]) + (size_t)sh.tiles * nft[k] * 64 * 2;
         hipLaunchKernelGGL(k_zero, dim3(64), dim3(256), 0, s, p, pad * nft[k]);

@@ -13,9 +13,11 @@
 // Derivative conventions: d|x|/dx = sign(x) (0 at 0); the clip of the action is handled
 // by the caller.
 //
-// Every function is a template on the real type T: the SHAC kernel uses float, a host
-// check instantiates double and compares each product with central differences of the
-// forward.  No HIP header is needed (AUV_HD marks host + device functions under hipcc).
+// The window kernel runs the same equations with four lanes per environment (shac_quad.hpp);
+// this form states them one environment at a time.  Every function is a template on the real
+// type T: a host check instantiates double, compares each product with central differences of
+// the forward, and compares the four-lane form with these.  No HIP header is needed (AUV_HD
+// marks host + device functions under hipcc).
 #pragma once
 
 #include <math.h>

@@ -23,3 +23,17 @@ def test_adjoint_products_match_finite_differences(tmp_path):
     assert out.returncode == 0, out.stdout
     assert out.stdout.strip().endswith("OK")
     assert out.stdout.count("max rel err") == 6
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_four_lane_form_matches_one_lane_form(tmp_path):
+    """The window kernel's four-lanes-per-environment physics and adjoint (csrc/shac_quad.hpp),
+    instantiated in double, against the one-lane form that the check above pins."""
+    exe = str(tmp_path / "quad_check")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-Werror", f"-I{CSRC}",
+                    os.path.join(HERE, "shac_quad_check.cpp"), "-o", exe], check=True)
+    out = subprocess.run([exe], capture_output=True, text=True)
+    print(out.stdout)
+    assert out.returncode == 0, out.stdout
+    assert out.stdout.strip().endswith("OK")
+    assert out.stdout.count("max rel err") == 6
