@@ -27,11 +27,12 @@
 //                  together.  Bound by the instruction stream of one wave per SIMD (at 4096
 //                  environments every CU holds one workgroup): with the physics in one-lane
 //                  form, every lane row a copy, and the RK4 stages re-integrated in the
-//                  reverse sweep, a 32-step window took 693 us in all; as it is, 457 us.  Each wave stores the bf16 operands of the weight gradient of its
-//                  features (q(h1), q(h2), q(dz2), q(dz1); wave 0 also q(o), q(gy)) as "half
-//                  fragments"
+//                  reverse sweep, a 32-step window took 693 us in all; with four lanes per
+//                  environment 457 us; with the small weight gradients summed here, in place
+//                  of a kernel that read 200 MB of their operands back, 398 us.  Each wave adds its features' dW1, dW3 and bias
+//                  gradients up in registers and stores the bf16 operands of dW2 (q(h1),
+//                  q(dz2)) as "half fragments"
 //   k_dw2          (PPO update) dW2 = sum q(dz2) q(h1)^T over all N h samples
-//   k_wsmall       dW1, dW3, the bias gradients and d log_std, per workgroup
 //   k_reduce       (PPO update) fixed-order sums of the partials -> packed gradient
 //   k_finalize     loss statistics, gradient norm, clipping factor
 //
@@ -57,7 +58,6 @@ constexpr int WAVES = 4;                 // waves per workgroup; wave w owns hid
 constexpr int WF = 32;                   // W2 (or W2^T) fragments of one wave: 4 M-tiles x 8 K steps
 constexpr int MAX_H = 64;                // window length bound
 constexpr int MAX_S = 4;                 // RK4 substeps per control step bound
-constexpr int TS = 20;                   // bf16 row stride of a transpose buffer
 constexpr int MODE_EXTERNAL = 0, MODE_MEAN = 2, MODE_SAMPLE = 3;
 
 // Fragment arrays of one network, in 64-lane fragments of 16 bytes per lane.
@@ -86,10 +86,10 @@ struct WinArgs {
   // (q, v, omega, and p in the first, 1 / |q| in the last), obk [h] (dpb, rotation vector, sk, kn), aa [h] (action components c and 3 + c
   // before clipping, their moving averages before the step)
   f32x4 *rec, *obk, *aa;
-  float *J, *Jr, *vl, *gls;
+  float *J, *Jr, *vl;
   f32x4* h2s;                          // policy hidden-2 activations [h][G][wave][M-tile][lane]
-  u32x2 *x_half, *h1_half, *h2_half, *gy_half, *dz2_half, *dz1_half;
-  int Np;
+  u32x2 *h1_half, *dz2_half;
+  int groups;                          // groups of 16 environments
   const float* ext;
   float *o_obs, *o_act, *o_reward, *o_done, *o_gact, *o_vlast, *o_gs0;
 };
@@ -98,7 +98,6 @@ struct Lds {
   bf16x8 W[WAVES][WF][64];    // per wave: its W2 fragments (forward sweep), then its W2^T ones (reverse)
   __bf16 X[WAVES][EPG][16];   // per wave: layer-1 inputs of the 16 environments (12 used, the rest zero)
   __bf16 G[WAVES][EPG][8];    // per wave: q(dL/dy)
-  __bf16 T[WAVES][32 * TS];   // per wave: transpose buffer [feature][environment]
   float Y[2][WAVES][EPG][8];  // output partials of each wave (two buffers, alternate steps)
   bf16x8 DZ[8][64];           // a B operand of all 256 hidden features (K step s: 32 s ..): hidden 1
                               // (forward), q(dz2) (reverse)
@@ -269,43 +268,55 @@ __device__ __forceinline__ f32x4 mlp_forward(const OwnF& O, const bf16x8* w2, co
   return mfma(O.w3[1], pack8(h2[2], h2[3]), y);
 }
 
-// Where the reverse sweep writes the weight-gradient operands of one step.
-struct HalfOut {
-  u32x2 *h1, *h2, *dz2, *dz1;
-  size_t tile;   // the workgroup's sample tile of this step
-  bool on;
+// The 0/1 selection operand: as B with a feature-major pair as A (lane (g, r): features
+// 16 (j / 4) + 4 g + j % 4 of sample r) it gives lane (g, r) feature 16 hf + r at samples
+// 4 g .. 4 g + 3, the half-fragment layout (exact: one nonzero product per output).
+__device__ __forceinline__ bf16x8 select_frag(int g, int r, int hf) {
+  bf16x8 f;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) f[j] = (__bf16)((g == (r >> 2) && j == 4 * hf + (r & 3)) ? 1.0f : 0.0f);
+  return f;
+}
+
+__device__ __forceinline__ u32x2 pack4(const f32x4& v) {
+  bf16x4 q;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) q[i] = (__bf16)v[i];
+  return __builtin_bit_cast(u32x2, q);
+}
+
+__device__ __forceinline__ bf16x8 low_half(u32x2 a) { return join2(a, u32x2{0u, 0u}); }
+
+// A wave's sums over its workgroup's samples of the small weight gradients of its 64 features
+// (M-tiles m; lane (g, r): rows 16 m + 4 g + i): dW1 (column r: input r, column ONES: db1), the
+// same product with q(dz2) (only its column ONES, db2, is used) and dW3^T (column r: output r);
+// and db3 (lane (g, r): output r over samples 4 g .. + 3 of every tile).
+constexpr int ONES = 12;   // the first padding input of the 12-input policy, set to 1 in the products' q(x)
+struct SmallGrads {
+  f32x4 w1[4], z2[4], w3[4];
+  float b3;
 };
 
-// D values of the M-tile pair (2c, 2c + 1) (features 32 c + 4 g + i and 32 c + 16 + 4 g + i,
-// environment r) -> bf16 half fragments of feature tiles 2c, 2c + 1 of the sample tile,
-// through wave w's transpose buffer.
-__device__ __forceinline__ void store_pair(Lds& S, int w, const f32x4& v0, const f32x4& v1, int lane, u32x2* dst,
-                                           size_t tile, int c) {
-  const int g = lane >> 4, r = lane & 15;
-  __bf16* T = S.T[w];
-  lds_sync();   // earlier readers of the buffer are done
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    T[(4 * g + i) * TS + r] = (__bf16)v0[i];
-    T[(16 + 4 * g + i) * TS + r] = (__bf16)v1[i];
-  }
-  lds_sync();
-#pragma unroll
-  for (int hf = 0; hf < 2; ++hf)
-    dst[(tile * 16 + 2 * c + hf) * 64 + lane] = *reinterpret_cast<const u32x2*>(&T[(16 * hf + r) * TS + 4 * g]);
-}
+// Where the reverse sweep writes the operands of dW2 of one step, and its small sums.
+struct HalfOut {
+  u32x2 *h1, *dz2;
+  size_t tile;       // the workgroup's sample tile of this step
+  bool on;           // a gradient is wanted
+  bf16x8 sel[2];     // select_frag
+};
 
 // Wave w's part of the backward pass from q(dL/dy) (GY, B operand with K = the output rows),
 // the layer-1 operand X and the wave's hidden-2 activations h2: dz2 of its features, given
 // to the other waves through LDS; dz1 = (W2^T q(dz2)) (1 - h1^2) of its hidden-1 features
 // (h1 recomputed from X); its partial of the input gradient W1^T q(dz1), and the sum of the
 // four waves' partials in wave order, gxo (inputs c, 3 + c, 6 + c, 9 + c of environment lane / 4,
-// c = min(lane mod 4, 2)).  With H.on it
-// also stores the weight-gradient operands of its features.  w2t: the wave's 32 W2^T
+// c = min(lane mod 4, 2)).  With
+// H.on it also stores q(dz2) and q(h1) of its features as half fragments and adds the
+// step's share of the small weight gradients.  w2t: the wave's 32 W2^T
 // fragments [M-tile m][K step s].
 __device__ __forceinline__ void mlp_backward(const OwnB& O, const bf16x8* w2t, const bf16x8& X, const bf16x8& GY,
                                              const f32x4 h2[4], int w, int lane, Lds& S, const HalfOut& H,
-                                             float gxo[4]) {
+                                             SmallGrads& sums, float gxo[4]) {
   const int g = lane >> 4, r = lane & 15;
   // hidden 2 (this wave's features): dz2 = (W3^T q(gy)) (1 - h2^2)
   f32x4 d[4];
@@ -315,13 +326,27 @@ __device__ __forceinline__ void mlp_backward(const OwnB& O, const bf16x8* w2t, c
 #pragma unroll
     for (int i = 0; i < 4; ++i) d[m][i] *= 1.0f - h2[m][i] * h2[m][i];
   }
-  S.DZ[2 * w][lane] = pack8(d[0], d[1]);
-  S.DZ[2 * w + 1][lane] = pack8(d[2], d[3]);
+  const bf16x8 pd[2] = {pack8(d[0], d[1]), pack8(d[2], d[3])};
+  S.DZ[2 * w][lane] = pd[0];
+  S.DZ[2 * w + 1][lane] = pd[1];
+  bf16x8 xh;
   if (H.on) {
-    store_pair(S, w, h2[0], h2[1], lane, H.h2, H.tile, 2 * w);
-    store_pair(S, w, h2[2], h2[3], lane, H.h2, H.tile, 2 * w + 1);
-    store_pair(S, w, d[0], d[1], lane, H.dz2, H.tile, 2 * w);
-    store_pair(S, w, d[2], d[3], lane, H.dz2, H.tile, 2 * w + 1);
+    const bf16x4 one = {(__bf16)1.0f, (__bf16)1.0f, (__bf16)1.0f, (__bf16)1.0f};
+    u32x2 xq = pack4(mfma(X, H.sel[0], zero4()));
+    if (r == ONES) xq = __builtin_bit_cast(u32x2, one);
+    xh = low_half(xq);
+    const f32x4 gyv = mfma(GY, H.sel[0], zero4());   // exact: bf16 values
+    const bf16x8 gyh = low_half(pack4(gyv));
+    sums.b3 += (gyv[0] + gyv[1]) + (gyv[2] + gyv[3]);
+    const bf16x8 ph[2] = {pack8(h2[0], h2[1]), pack8(h2[2], h2[3])};
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const bf16x8 h2h = low_half(pack4(mfma(ph[m >> 1], H.sel[m & 1], zero4())));
+      sums.w3[m] = mfma(h2h, gyh, sums.w3[m]);
+      const u32x2 dh = pack4(mfma(pd[m >> 1], H.sel[m & 1], zero4()));
+      H.dz2[(H.tile * 16 + 4 * w + m) * 64 + lane] = dh;
+      sums.z2[m] = mfma(low_half(dh), xh, sums.z2[m]);
+    }
   }
   wg_sync();
   // hidden 1 (this wave's features): dz1 = (W2^T q(dz2)) (1 - h1^2), h1 recomputed
@@ -343,16 +368,19 @@ __device__ __forceinline__ void mlp_backward(const OwnB& O, const bf16x8* w2t, c
       e[m][i] *= 1.0f - k[m][i] * k[m][i];
     }
   }
-  if (H.on) {
-    store_pair(S, w, k[0], k[1], lane, H.h1, H.tile, 2 * w);
-    store_pair(S, w, k[2], k[3], lane, H.h1, H.tile, 2 * w + 1);
-    store_pair(S, w, e[0], e[1], lane, H.dz1, H.tile, 2 * w);
-    store_pair(S, w, e[2], e[3], lane, H.dz1, H.tile, 2 * w + 1);
-  }
   // input gradient: the partial over this wave's hidden-1 features (M-tile 0: inputs 0..15)
-  f32x4 gx = mfma(O.w1t[0], pack8(e[0], e[1]), zero4());
-  gx = mfma(O.w1t[1], pack8(e[2], e[3]), gx);
+  const bf16x8 pe[2] = {pack8(e[0], e[1]), pack8(e[2], e[3])};
+  const f32x4 gx = mfma(O.w1t[1], pe[1], mfma(O.w1t[0], pe[0], zero4()));
   *reinterpret_cast<f32x4*>(&S.GX[w][r][4 * g]) = gx;
+  if (H.on) {
+    const bf16x8 pk[2] = {pack8(k[0], k[1]), pack8(k[2], k[3])};
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      H.h1[(H.tile * 16 + 4 * w + m) * 64 + lane] = pack4(mfma(pk[m >> 1], H.sel[m & 1], zero4()));
+      const bf16x8 eh = low_half(pack4(mfma(pe[m >> 1], H.sel[m & 1], zero4())));
+      sums.w1[m] = mfma(eh, xh, sums.w1[m]);
+    }
+  }
   wg_sync();
   const int slot = lane >> 2, c = min(lane & 3, 2);
 #pragma unroll
@@ -413,19 +441,6 @@ __device__ __forceinline__ float out_sum(const Lds& S, int b, int r, int j) {
   return s;
 }
 
-// Half fragments of wave 0's layer-1 inputs (one feature tile: inputs 16.. are zero) and of
-// q(gy) (one tile).
-__device__ __forceinline__ void store_input_halves(const Lds& S, int lane, u32x2* xh, u32x2* gh, size_t tile) {
-  const int g = lane >> 4, r = lane & 15;
-  bf16x4 v;
-#pragma unroll
-  for (int s = 0; s < 4; ++s) v[s] = S.X[0][4 * g + s][r];
-  xh[tile * 64 + lane] = __builtin_bit_cast(u32x2, v);
-#pragma unroll
-  for (int s = 0; s < 4; ++s) v[s] = r < 8 ? S.G[0][4 * g + s][r & 7] : (__bf16)0.0f;
-  gh[tile * 64 + lane] = __builtin_bit_cast(u32x2, v);
-}
-
 // ------------------------------------------------------------------ environment --------
 // This lane's model constants (component c of each triple, zero in lane 3): no current, weight
 // gamma W (gamma in parameter row 13), buoyancy centre at the centre of gravity.
@@ -462,7 +477,7 @@ __device__ __forceinline__ void paper_noise(const EnvArgs& E, uint32_t gid, uint
 
 // ------------------------------------------------------------------ window kernel ------
 template <int MODE>
-__global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, WinArgs A) {
+__global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, WinArgs A, GradParts P_) {
   __shared__ Lds S;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -470,22 +485,39 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
   const int slot = lane >> 2, c = lane & 3;    // lane of the four-lane physics
   const quad::QK Q = quad::make_qk(lane);
   const qadj::LaneK<float> K{Q.m3, 1.0f - Q.m3, Q.e1, Q.e2, Q.d2};
-  const int i = blockIdx.x * EPG + slot;
   const int N = E.n;
+  const size_t Nz = (size_t)N;
+  const int h = A.steps;
+  if (threadIdx.x <= MAX_H) S.pw[threadIdx.x] = powf(A.gamma, (float)threadIdx.x);
+  for (int k = threadIdx.x; k < WAVES * EPG * 16; k += 64 * WAVES) (&S.X[0][0][0])[k] = (__bf16)0.0f;
+  for (int k = threadIdx.x; k < WAVES * EPG * 8; k += 64 * WAVES) (&S.G[0][0][0])[k] = (__bf16)0.0f;
+  SmallGrads sums;
+#pragma unroll
+  for (int m = 0; m < 4; ++m) sums.w1[m] = sums.z2[m] = sums.w3[m] = zero4();
+  sums.b3 = 0.0f;
+  HalfOut H{A.h1_half, A.dz2_half, 0, MODE != MODE_EXTERNAL && A.want_grad,
+            {select_frag(g, r, 0), select_frag(g, r, 1)}};
+  float gls0 = 0.0f, gls1 = 0.0f;   // d log sigma of actions c and 3 + c
+  const size_t G = (size_t)A.groups;
+
+  // one group of 16 environments after another (a workgroup's LDS fills its CU, so groups past
+  // the CUs would run in turn anyway; the small gradients' sums stay in registers)
+#pragma unroll 1
+  for (int grp = blockIdx.x; grp < A.groups; grp += gridDim.x) {
+  const int i = grp * EPG + slot;
   const bool valid = i < N;
   const int ic = valid ? i : N - 1;            // idle slots step a copy of the last environment
-  const size_t Nz = (size_t)N, Np = (size_t)A.Np;
-  const int h = A.steps;
   const uint32_t gid = E.env_offset + (uint32_t)i;
+  // the networks as this group reads them: loads not hoisted out of the loop over groups, where
+  // both sweeps' weights would be live at once
+  NetF pol = A.pol, val = A.val;
+  asm volatile("" : "+s"(pol.f), "+s"(pol.b), "+s"(val.f), "+s"(val.b));
   // wave 0 writes the state's results, wave 1 the recorded observations, wave 2 the actions and
   // their gradients, wave 3 rewards and done flags (every wave holds all of them)
   const bool w_obs = w == 1 && valid && A.o_obs, w_act = w == 2 && valid && A.o_act;
   const bool w_gact = w == 2 && valid && A.o_gact, w_rew = w == 3 && valid && c == 0;
 
-  if (threadIdx.x <= MAX_H) S.pw[threadIdx.x] = powf(A.gamma, (float)threadIdx.x);
-  for (int k = threadIdx.x; k < WAVES * EPG * 16; k += 64 * WAVES) (&S.X[0][0][0])[k] = (__bf16)0.0f;
-  for (int k = threadIdx.x; k < WAVES * EPG * 8; k += 64 * WAVES) (&S.G[0][0][0])[k] = (__bf16)0.0f;
-  wg_sync();
+  wg_sync();   // LDS set up, or the group before done with it
 
   // environment of this quad: row k of a 3-vector in lanes c < 3, zero in lane 3
   auto row3 = [&](const float* p, int k) { return c < 3 ? p[(size_t)(k + min(c, 2)) * Nz + ic] : 0.0f; };
@@ -509,21 +541,21 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
       sig1 = expf(A.log_std[3 + c]);
     }
     if (MODE != MODE_EXTERNAL) {
-      b30 = A.pol.b[2 * HID + c];
-      b31 = A.pol.b[2 * HID + 3 + c];
+      b30 = pol.b[2 * HID + c];
+      b31 = pol.b[2 * HID + 3 + c];
     }
   }
   // where this workgroup's lanes keep the forward sweep's records
-  const size_t G = gridDim.x, at0 = (size_t)blockIdx.x * 64 + lane;
+  const size_t at0 = (size_t)grp * 64 + lane;
   auto rec_at = [&](int t, int s, int stage) { return A.rec + (((size_t)t * E.substeps + s) * 4 + stage) * G * 64 + at0; };
   auto row_at = [&](f32x4* a, int t) { return a + (size_t)t * G * 64 + at0; };
-  auto h2_at = [&](int t) { return A.h2s + (((size_t)t * G + blockIdx.x) * WAVES + w) * H2_F4 + lane; };
+  auto h2_at = [&](int t) { return A.h2s + (((size_t)t * G + grp) * WAVES + w) * H2_F4 + lane; };
 
   // ---------------------------------------------------------------- forward sweep
   OwnF of{};
   if (MODE != MODE_EXTERNAL) {
-    fill_w(S, A.pol, F_W2 + WF * w, w, lane);
-    of = own_fwd(A.pol, w, lane);
+    fill_w(S, pol, F_W2 + WF * w, w, lane);
+    of = own_fwd(pol, w, lane);
   }
   float Jr = 0.0f;
   qadj::QObsK<float> o = qadj::observe(K, p, x.q, pg, qg);
@@ -588,8 +620,9 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
       const float p0 = p;
       qadj::substep(K, M, tfi, tm, E.h, p, x, st, inv);
       // wave w stores stage w's input
-      const qadj::QX<float> mine = w == 0 ? st[0] : (w == 1 ? st[1] : (w == 2 ? st[2] : st[3]));
-      *rec_at(t, s, w) = f32x4{mine.q, mine.v, mine.w, w == 0 ? p0 : inv};
+      auto mine = [&](float s0, float s1, float s2, float s3) { return w == 0 ? s0 : (w == 1 ? s1 : (w == 2 ? s2 : s3)); };
+      *rec_at(t, s, w) = f32x4{mine(st[0].q, st[1].q, st[2].q, st[3].q), mine(st[0].v, st[1].v, st[2].v, st[3].v),
+                               mine(st[0].w, st[1].w, st[2].w, st[3].w), w == 0 ? p0 : inv};
     }
     o = qadj::observe(K, p, x.q, pg, qg);
     const quad::QObs ob{o.dpb, o.rv, 0.0f};
@@ -614,13 +647,14 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
     lds_sync();
     const bf16x8 X = input_frag(S, w, lane), GY = gy_frag(S, w, lane);
     f32x4 h2[4];
-    const f32x4 y = mlp_forward(own_fwd(A.val, w, lane), A.val.f + (size_t)(F_W2 + WF * w) * 64, X, w, lane, S, h2);
+    const f32x4 y = mlp_forward(own_fwd(val, w, lane), val.f + (size_t)(F_W2 + WF * w) * 64, X, w, lane, S, h2);
     const int b = h & 1;
     if (g < 2) *reinterpret_cast<f32x4*>(&S.Y[b][w][r][4 * g]) = y;
     wg_sync();
-    vlast = out_sum(S, b, slot, 0) + A.val.b[2 * HID];
-    const HalfOut off{nullptr, nullptr, nullptr, nullptr, 0, false};
-    mlp_backward(own_bwd(A.val, w, lane), A.val.f + (size_t)(F_W2T + WF * w) * 64, X, GY, h2, w, lane, S, off, go);
+    vlast = out_sum(S, b, slot, 0) + val.b[2 * HID];
+    HalfOut off = H;
+    off.on = false;
+    mlp_backward(own_bwd(val, w, lane), val.f + (size_t)(F_W2T + WF * w) * 64, X, GY, h2, w, lane, S, off, sums, go);
   }
 
   // ------------------------------------------- environment update (reset at the episode end)
@@ -663,8 +697,8 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
   // ---------------------------------------------------------------- reverse sweep
   OwnB ob{};
   if (MODE != MODE_EXTERNAL) {
-    fill_w(S, A.pol, F_W2T + WF * w, w, lane);
-    ob = own_bwd(A.pol, w, lane);
+    fill_w(S, pol, F_W2T + WF * w, w, lane);
+    ob = own_bwd(pol, w, lane);
   }
   float lp = 0.0f;
   qadj::QX<float> l{0.0f, 0.0f, 0.0f};
@@ -685,7 +719,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
   float cr = valid ? -S.pw[h - 1] * A.inv_nh : 0.0f;   // weight of the reward r_t being taken backward
   through_obs(h - 1, cr, o, p, x);
   float qn = x.q;                                        // the quaternion at the end of the substep
-  float la0 = 0.0f, la1 = 0.0f, gls0 = 0.0f, gls1 = 0.0f;
+  float la0 = 0.0f, la1 = 0.0f;
   f32x4 rs[4];                                           // the substep's stage records, loaded one substep ahead
 #pragma unroll
   for (int k = 0; k < 4; ++k) rs[k] = *rec_at(h - 1, E.substeps - 1, k);
@@ -752,10 +786,8 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
       put_gy(S, w, lane, ga0, ga1);
       lds_sync();
       const bf16x8 X = input_frag(S, w, lane), GY = gy_frag(S, w, lane);
-      const size_t tile = (size_t)t * G + blockIdx.x;
-      if (A.want_grad && w == 0) store_input_halves(S, lane, A.x_half, A.gy_half, tile);
-      const HalfOut H{A.h1_half, A.h2_half, A.dz2_half, A.dz1_half, tile, A.want_grad != 0};
-      mlp_backward(ob, &S.W[w][0][0], X, GY, h2, w, lane, S, H, go);
+      H.tile = (size_t)t * G + grp;
+      mlp_backward(ob, &S.W[w][0][0], X, GY, h2, w, lane, S, H, sums, go);
     }
     cr = (valid && t > 0) ? -S.pw[t > 0 ? t - 1 : 0] * A.inv_nh : 0.0f;
     through_obs(t - 1, cr, ok, pt, x0);
@@ -768,126 +800,48 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
     }
     A.o_gs0[(size_t)(c < 3 ? 4 + c : 3) * Nz + i] = l.q;
   }
-  if (w == 0) {
-    if (c == 0) {
-      A.J[i] = valid ? __builtin_fmaf(S.pw[h], vlast, Jr) : 0.0f;
-      A.Jr[i] = valid ? Jr : 0.0f;
-      A.vl[i] = valid ? vlast : 0.0f;
-    }
-    // rows 6, 7: padding
-    A.gls[(size_t)(c < 3 ? c : 6) * Np + i] = (valid && c < 3) ? gls0 : 0.0f;
-    A.gls[(size_t)(c < 3 ? 3 + c : 7) * Np + i] = (valid && c < 3) ? gls1 : 0.0f;
+  if (w == 0 && c == 0) {
+    A.J[i] = valid ? __builtin_fmaf(S.pw[h], vlast, Jr) : 0.0f;
+    A.Jr[i] = valid ? Jr : 0.0f;
+    A.vl[i] = valid ? vlast : 0.0f;
   }
-}
-
-// ------------------------------------------------------------------ small products -----
-// Over the K steps (32 samples = two sample tiles) [u0, u1) of this workgroup:
-// dW1 = sum q(dz1) q(o)^T, dW3^T = sum q(h2) q(gy)^T, db1 = sum q(dz1), db2 = sum q(dz2),
-// db3 = sum q(gy); and d log_std = sum over this workgroup's share of the environments.
-// Four waves: wave w owns hidden features 64 w .. 64 w + 63 (M-tiles 4w .. 4w + 3).
-__device__ __forceinline__ float sum8(const bf16x8& v) {
-  float s = 0.0f;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) s += (float)v[j];
-  return s;
-}
-
-__global__ __launch_bounds__(256) void k_wsmall(const u32x2* __restrict__ x_half, const u32x2* __restrict__ gy_half,
-                                                const u32x2* __restrict__ h2_half, const u32x2* __restrict__ dz2_half,
-                                                const u32x2* __restrict__ dz1_half, const float* __restrict__ gls,
-                                                int steps, int Np, GradParts P) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int g = lane >> 4, r = lane & 15;
-  const int per = (steps + gridDim.x - 1) / gridDim.x;
-  const int u0 = blockIdx.x * per, u1 = min(steps, u0 + per);
-  f32x4 w1[4], w3[4];
-  float b1[4], b2[4], b3 = 0.0f;
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
-    w1[mt] = w3[mt] = zero4();
-    b1[mt] = b2[mt] = 0.0f;
   }
-  auto at = [&](int tile, int ft, int nft) { return ((size_t)tile * nft + ft) * 64 + lane; };
-  // operands of one K step (sample tiles 2u, 2u + 1), loaded one K step ahead
-  struct In {
-    u32x2 x[2], gy[2], d1[4][2], h2[4][2], d2[4][2];
-  };
-  auto load = [&](int u, In& v) {
+
+  // ------------------------------------------------ this workgroup's small gradient sums
+  if (MODE == MODE_EXTERNAL || !A.want_grad) return;
+  const size_t wg = blockIdx.x;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int tl = 2 * u + k;
-      v.x[k] = x_half[at(tl, 0, 1)];
-      v.gy[k] = gy_half[at(tl, 0, 1)];
+  for (int m = 0; m < 4; ++m)
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        const int ft = 4 * w + mt;
-        v.d1[mt][k] = dz1_half[at(tl, ft, 16)];
-        v.h2[mt][k] = h2_half[at(tl, ft, 16)];
-        v.d2[mt][k] = dz2_half[at(tl, ft, 16)];
+    for (int q = 0; q < 4; ++q) {
+      const size_t f = wg * HID + 64 * w + 16 * m + 4 * g + q;
+      P_.part_w1[f * 32 + r] = r < ONES ? sums.w1[m][q] : 0.0f;
+      P_.part_w1[f * 32 + 16 + r] = 0.0f;   // inputs 12.. of the paper task are zero
+      P_.part_w3t[f * 16 + r] = sums.w3[m][q];
+      if (r == ONES) {
+        P_.part_b1[f] = sums.w1[m][q];
+        P_.part_b2[f] = sums.z2[m][q];
       }
     }
-  };
-  In cur;
-  if (u0 < u1) load(u0, cur);
-  for (int u = u0; u < u1; ++u) {
-    In nxt;
-    load(min(u + 1, u1 - 1), nxt);   // unconditional (clamped), so no wait covers it early
-    const bf16x8 xb = join2(cur.x[0], cur.x[1]);
-    const bf16x8 gb = join2(cur.gy[0], cur.gy[1]);
-    if (w == 0) b3 += sum8(gb);
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const bf16x8 d1 = join2(cur.d1[mt][0], cur.d1[mt][1]);
-      const bf16x8 h2 = join2(cur.h2[mt][0], cur.h2[mt][1]);
-      const bf16x8 d2 = join2(cur.d2[mt][0], cur.d2[mt][1]);
-      w1[mt] = mfma(d1, xb, w1[mt]);
-      w3[mt] = mfma(h2, gb, w3[mt]);
-      b1[mt] += sum8(d1);
-      b2[mt] += sum8(d2);
-    }
-    cur = nxt;
-  }
-  const int G = blockIdx.x;
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int k = 64 * w + 16 * mt + 4 * g + i;
-      P.part_w1[((size_t)G * HID + k) * 32 + r] = w1[mt][i];
-      P.part_w1[((size_t)G * HID + k) * 32 + 16 + r] = 0.0f;   // inputs 16.. of the paper task are zero
-      P.part_w3t[((size_t)G * HID + k) * 16 + r] = w3[mt][i];
-    }
-    // lanes (g, r), g = 0..3, hold partial sums of feature 16 (4w + mt) + r: add in g order
-    float s1 = b1[mt], s2 = b2[mt];
-    s1 += __shfl_xor(s1, 16);
-    s2 += __shfl_xor(s2, 16);
-    s1 += __shfl_xor(s1, 32);
-    s2 += __shfl_xor(s2, 32);
-    if (g == 0) {
-      P.part_b1[(size_t)G * HID + 64 * w + 16 * mt + r] = s1;
-      P.part_b2[(size_t)G * HID + 64 * w + 16 * mt + r] = s2;
-    }
-  }
   if (w == 0) {
-    float s = b3;
-    s += __shfl_xor(s, 16);
-    s += __shfl_xor(s, 32);
-    if (g == 0) P.part_b3[(size_t)G * 16 + r] = s;
-  } else if (w == 1) {
-    // d log_std: this workgroup's share of the environments, lane-strided, then a wave sum
-    const int per_e = (Np + gridDim.x - 1) / gridDim.x;
-    const int e0 = G * per_e, e1 = min(Np, e0 + per_e);
+    float b3 = sums.b3;   // over the lane rows g, in a fixed order
+    b3 += __shfl_xor(b3, 16);
+    b3 += __shfl_xor(b3, 32);
+    if (g == 0) P_.part_b3[wg * 16 + r] = b3;
+    float d0 = gls0, d1 = gls1;   // over the wave's 16 environments
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      float s = 0.0f;
-      if (j < 8)
-        for (int e = e0 + lane; e < e1; e += 64) s += gls[(size_t)j * Np + e];
-      s = wave_sum(s);
-      if (lane == 0) P.part_ls[(size_t)G * 16 + j] = s;
+    for (int o = 4; o < 64; o *= 2) {
+      d0 += __shfl_xor(d0, o);
+      d1 += __shfl_xor(d1, o);
+    }
+    if (slot == 0) {
+      P_.part_ls[wg * 16 + (c < 3 ? c : 6)] = c < 3 ? d0 : 0.0f;
+      P_.part_ls[wg * 16 + (c < 3 ? 3 + c : 7)] = c < 3 ? d1 : 0.0f;
     }
   }
 }
 
+// ------------------------------------------------------------------ statistics ---------
 // stats: [0] loss, [1] mean over envs of sum_t gamma^t r_t, [2] mean V(o_h), [5] |grad|^2,
 // [7] clipping factor min(1, c / (|grad| + 1e-6)) (1 without clipping or without gradient).
 // One workgroup of four waves; every sum in a fixed order (thread-strided with four loads in
@@ -937,11 +891,11 @@ __global__ __launch_bounds__(256) void k_zero(uint32_t* __restrict__ p, size_t n
 
 // ------------------------------------------------------------------ workspace ----------
 inline size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
-constexpr int WORK_PARTS = 22;
+constexpr int WORK_PARTS = 17;
 constexpr int MAX_GROUPS = 256;
 
 struct Shape {
-  int NG, Np, tiles, tiles_p, steps, GS, G3;
+  int NG, Np, tiles, tiles_p, steps, GW, G3;
 };
 
 inline Shape shape_of(int N, int h, int cus) {
@@ -951,7 +905,7 @@ inline Shape shape_of(int N, int h, int cus) {
   s.tiles = h * s.NG;
   s.tiles_p = (s.tiles + 7) / 8 * 8;     // whole rounds of the dW2 loop (4 steps of 2 tiles)
   s.steps = s.tiles_p / 2;
-  s.GS = std::max(1, std::min({MAX_GROUPS, s.steps, cus}));
+  s.GW = std::min({MAX_GROUPS, s.NG, cus});   // workgroups of the window
   s.G3 = std::max(1, std::min({MAX_GROUPS, s.steps / 4, cus}));
   return s;
 }
@@ -964,15 +918,14 @@ inline size_t work_layout(int N, int h, size_t off[WORK_PARTS]) {
       (size_t)h * (Np / EPG) * 64 * 16,   // 1 observations with their derivative factors
       (size_t)h * (Np / EPG) * 64 * 16,     // 2 actions and action averages
       Np * 4, Np * 4, Np * 4,               // 3 J, 4 Jr, 5 V(o_h)
-      8 * Np * 4,                           // 6 d log_std per environment
-      half, half, half * 16, half * 16, half * 16, half * 16,   // 7 x, 8 gy, 9 h1, 10 h2, 11 dz2, 12 dz1
-      G * HID * 32 * 4, G * HID * 4,        // 13 part_w1, 14 part_b1
-      G * HID * 16 * 4, G * HID * 4,        // 15 part_w3t, 16 part_b2
-      G * 16 * 4 + G * 16 * 4,              // 17 part_b3 + part_ls
-      G * HID * HID * 4,                    // 18 part_w2
-      4096 * 4,                             // 19 per-block sums of squares
-      (size_t)h * (Np / EPG) * WAVES * H2_F4 * 16,   // 20 policy hidden-2 activations
-      (size_t)h * MAX_S * 4 * (Np / EPG) * 64 * 16};   // 21 RK4 stage inputs
+      half * 16, half * 16,                 // 6 h1, 7 dz2
+      G * HID * 32 * 4, G * HID * 4,        // 8 part_w1, 9 part_b1
+      G * HID * 16 * 4, G * HID * 4,        // 10 part_w3t, 11 part_b2
+      G * 16 * 4 + G * 16 * 4,              // 12 part_b3 + part_ls
+      G * HID * HID * 4,                    // 13 part_w2
+      4096 * 4,                             // 14 per-block sums of squares
+      (size_t)h * (Np / EPG) * WAVES * H2_F4 * 16,   // 15 policy hidden-2 activations
+      (size_t)h * MAX_S * 4 * (Np / EPG) * 64 * 16};   // 16 RK4 stage inputs
   size_t o = 0;
   for (int k = 0; k < WORK_PARTS; ++k) {
     off[k] = o;
@@ -1069,16 +1022,11 @@ int auv_shac_window(auv_env* env, const auv_shac_config* cfg, const auv_mlp* pol
   A.J = (float*)at(3);
   A.Jr = (float*)at(4);
   A.vl = (float*)at(5);
-  A.gls = (float*)at(6);
-  A.x_half = (u32x2*)at(7);
-  A.gy_half = (u32x2*)at(8);
-  A.h1_half = (u32x2*)at(9);
-  A.h2_half = (u32x2*)at(10);
-  A.dz2_half = (u32x2*)at(11);
-  A.dz1_half = (u32x2*)at(12);
-  A.h2s = (f32x4*)at(20);
-  A.rec = (f32x4*)at(21);
-  A.Np = sh.Np;
+  A.h1_half = (u32x2*)at(6);
+  A.dz2_half = (u32x2*)at(7);
+  A.h2s = (f32x4*)at(15);
+  A.rec = (f32x4*)at(16);
+  A.groups = sh.NG;
   if (out) {
     A.ext = out->actions;
     A.o_obs = out->obs;
@@ -1089,38 +1037,33 @@ int auv_shac_window(auv_env* env, const auv_shac_config* cfg, const auv_mlp* pol
     A.o_vlast = out->value_last;
     A.o_gs0 = out->grad_state0;
   }
+  GradParts P;
+  P.part_w1 = (float*)at(8);
+  P.part_b1 = (float*)at(9);
+  P.part_w3t = (float*)at(10);
+  P.part_b2 = (float*)at(11);
+  P.part_b3 = (float*)at(12);
+  P.part_ls = P.part_b3 + MAX_GROUPS * 16;
+  P.part_w2 = (float*)at(13);
+  const dim3 wgrid(sh.GW), wblock(64 * WAVES);
   if (mode == AUV_ACT_EXTERNAL)
-    hipLaunchKernelGGL(k_window<MODE_EXTERNAL>, dim3(sh.NG), dim3(64 * WAVES), 0, s, env->E, env->veh, A);
+    hipLaunchKernelGGL(k_window<MODE_EXTERNAL>, wgrid, wblock, 0, s, env->E, env->veh, A, P);
   else if (mode == AUV_ACT_POLICY_MEAN)
-    hipLaunchKernelGGL(k_window<MODE_MEAN>, dim3(sh.NG), dim3(64 * WAVES), 0, s, env->E, env->veh, A);
+    hipLaunchKernelGGL(k_window<MODE_MEAN>, wgrid, wblock, 0, s, env->E, env->veh, A, P);
   else
-    hipLaunchKernelGGL(k_window<MODE_SAMPLE>, dim3(sh.NG), dim3(64 * WAVES), 0, s, env->E, env->veh, A);
+    hipLaunchKernelGGL(k_window<MODE_SAMPLE>, wgrid, wblock, 0, s, env->E, env->veh, A, P);
 
   const int rb = grad_reduce_blocks(ACT);
-  float* ss = (float*)at(19);
+  float* ss = (float*)at(14);
   if (grad_policy) {
     // padding sample tiles (beyond the window's) hold zeros and so add nothing
     if (sh.tiles_p > sh.tiles) {
-      const size_t pad = (size_t)(sh.tiles_p - sh.tiles) * 64 * 2;   // u32 per tile and feature tile
-      const int parts[6] = {7, 8, 9, 10, 11, 12};
-      const int nft[6] = {1, 1, 16, 16, 16, 16};
-      for (int k = 0; k < 6; ++k) {
-        uint32_t* p = (uint32_t*)at(parts[k]) + (size_t)sh.tiles * nft[k] * 64 * 2;
-        hipLaunchKernelGGL(k_zero, dim3(64), dim3(256), 0, s, p, pad * nft[k]);
-      }
+      const size_t pad = (size_t)(sh.tiles_p - sh.tiles) * 16 * 64 * 2;   // u32
+      for (u32x2* half : {A.h1_half, A.dz2_half})
+        hipLaunchKernelGGL(k_zero, dim3(64), dim3(256), 0, s, (uint32_t*)(half + (size_t)sh.tiles * 16 * 64), pad);
     }
-    GradParts P;
-    P.part_w1 = (float*)at(13);
-    P.part_b1 = (float*)at(14);
-    P.part_w3t = (float*)at(15);
-    P.part_b2 = (float*)at(16);
-    P.part_b3 = (float*)at(17);
-    P.part_ls = P.part_b3 + MAX_GROUPS * 16;
-    P.part_w2 = (float*)at(18);
     if (int rc = launch_dw2(A.dz2_half, A.h1_half, sh.steps, sh.G3, P.part_w2, s)) return rc;
-    hipLaunchKernelGGL(k_wsmall, dim3(sh.GS), dim3(256), 0, s, A.x_half, A.gy_half, A.h2_half, A.dz2_half, A.dz1_half,
-                       A.gls, sh.steps, sh.Np, P);
-    if (int rc = launch_grad_reduce(P, ACT, 6, sh.GS, sh.GS, sh.G3, grad_policy, ss, s)) return rc;
+    if (int rc = launch_grad_reduce(P, ACT, 6, sh.GW, sh.GW, sh.G3, grad_policy, ss, s)) return rc;
   }
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(256), 0, s, A.J, A.Jr, A.vl, N, A.inv_nh, ss, grad_policy ? rb : 0,
                      cfg->max_grad_norm, stats);

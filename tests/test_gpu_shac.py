@@ -363,6 +363,37 @@ def test_shac_full_size_sampled_envs():
     assert _block_err(ga[:, :, idx], want["grad_act"] * scale) <= 5e-2
 
 
+def test_shac_more_groups_than_workgroups():
+    """8192 environments are two 16-environment groups for each of 256 workgroups, which then run
+    in turn and add up the small gradients of both.  Each half as a handle of its own gives every
+    environment the same bits (the objective's weight is exactly doubled), and the mean of
+    the halves' gradients up to the order of fp32 sums."""
+    n, h = 8192, 3
+    announce(f"SHAC grouped window n={n}")
+    require_gpu()
+    x0 = torch.from_numpy(W.random_states(n, seed=4))
+
+    def run(off, m):
+        g = gpu_env(W.config("c6", n_envs=m, env_offset=off))
+        g.set_task(W.PAPER_TASK)
+        g.reset()
+        g.state.copy_(x0[:, off:off + m])
+        L = _learner(g, h)
+        out = dict(act=_dev(8, h, m), grad_act=_dev(8, h, m), grad_state0=_dev(13, m), value_last=_dev(m))
+        L.window(out=out)
+        return L.grad.clone(), dict(out, state=g.state, params=g.params)
+
+    grad, full = run(0, n)
+    halves = [run(0, n // 2), run(n // 2, n // 2)]
+    for k, v in full.items():
+        both = torch.cat([q[k] for _, q in halves], dim=-1)
+        scale = 0.5 if k.startswith("grad") else 1.0
+        assert torch.equal(v, scale * both), k
+    want = 0.5 * (halves[0][0].double() + halves[1][0].double())
+    bound = 2.0 ** -24 * np.sqrt(n * h) * 4   # a fixed-order fp32 sum over the samples, random signs
+    assert (grad.double() - want).abs().max() <= bound * want.abs().max()
+
+
 def test_shac_critic_regression():
     """The critic's value-only gradient equals the value part of a full PPO gradient call on
     the same minibatch (same kernels, bit for bit); TD(lambda) targets are consistent
