@@ -9,12 +9,11 @@
 //                   the policy's k_vtile turns them into the mean and 1 / (std + 1e-8))
 // then for each network (the value net alone in every minibatch of auv_ppo_fit_value):
 //   k_vtile<n>      per 16-sample tile and wave, the weights in LDS: forward, loss (clipped
-//                   surrogate for n = 8, squared error for n = 1), dL/dy, dz2, dz1; the sums of
-//                   the bias and output-layer gradients (and of d log sigma and the loss
-//                   statistics); q(x) as the layer-1 operand and half fragments of q(dz2),
-//                   q(dz1) for the weight-gradient product
-//   k_vwgrad        dW2 and dW1 per (64- or 128-row block, chunk of the minibatch), q(h1)
-//                   stored or recomputed from q(x)
+//                   surrogate for n = 8, squared error for n = 1), dL/dy, dz2; the sums of db2 and
+//                   the output-layer gradients (and of d log sigma and the loss statistics); q(x)
+//                   as the layer-1 operand and q(dz2) as half fragments
+//   k_wgrad         per (column block, chunk of the minibatch): dh1 = W2^T q(dz2), dz1, and the
+//                   products over the samples dW2, dW1, db1
 //   k_reduce        fixed-order sums of the partials -> packed gradient, and per-block sums of
 //                   squares (with the Adam step fused in a value-only fit)
 // and last
@@ -76,9 +75,10 @@ struct Work {
   float* part_b1;       // [G][256]
   float* part_w2;       // [G][256 m][256 k]
   float* part_ss;       // [2 nets][reduce blocks]
-  u32x2* dz1_half;      // [Bp/16][16 feature tiles][64 lanes] q(dz1) half fragments
   bf16x8* x_frag;       // [Bp/16][64 lanes] q(x) as the layer-1 operand (lane (g, r): inputs
                         // kslot(g, j) of sample r, zero past the 23 inputs and the batch)
+  // the value net below VALUE_LATER_STEPS:
+  u32x2* dz1_half;      // [Bp/16][16 feature tiles][64 lanes] q(dz1) half fragments
   u32x2* h1_half;       // [Bp/16][16 feature tiles][64 lanes] q(h1) half fragments, stored only
                         // below VW_RECOMP_STEPS steps (above, k_vwgrad recomputes q(h1))
 };
@@ -96,8 +96,7 @@ inline int nparam(int n_out) { return HID * 23 + HID * HID + n_out * HID + 2 * H
 inline int red_blocks(int n_out) { return (nparam(n_out) + RED_ELEMS - 1) / RED_ELEMS; }
 
 // Byte offsets of the workspace parts for a minibatch of B; returns the total.
-// From this many 32-sample steps on, the weight-gradient product recomputes q(h1) instead of
-// storing it (see k_vwgrad).
+// From this many 32-sample steps on, k_vwgrad recomputes q(h1) instead of reading it.
 constexpr int VW_RECOMP_STEPS = 4096;
 constexpr int WORK_PARTS = 14;
 inline size_t work_layout(int B, size_t off[WORK_PARTS]) {
@@ -107,7 +106,7 @@ inline size_t work_layout(int B, size_t off[WORK_PARTS]) {
                             G * HID * 16 * 4, G * HID * 4, G * 16 * 4, G * 16 * 4, 2 * G * STATS * 4,
                             G * HID * 32 * 4, G * HID * 4, G * HID * HID * 4,
                             2 * (size_t)red_blocks(8) * 4,
-                            Bp * HID * 2, Bp / 16 * 64 * 16, recomp ? 0 : Bp * HID * 2};
+                            Bp / 16 * 64 * 16, Bp * HID * 2, recomp ? 0 : Bp * HID * 2};
   size_t o = 0;
   for (int k = 0; k < WORK_PARTS; ++k) {
     off[k] = o;
@@ -132,8 +131,8 @@ inline Work work_at(void* base, int B) {
   W.part_b1 = (float*)(p + off[8]);
   W.part_w2 = (float*)(p + off[9]);
   W.part_ss = (float*)(p + off[10]);
-  W.dz1_half = (u32x2*)(p + off[11]);
-  W.x_frag = (bf16x8*)(p + off[12]);
+  W.x_frag = (bf16x8*)(p + off[11]);
+  W.dz1_half = (u32x2*)(p + off[12]);
   W.h1_half = (u32x2*)(p + off[13]);
   return W;
 }
@@ -290,29 +289,35 @@ __global__ __launch_bounds__(64 * DW2_WAVES, 1) void k_dw2(const u32x2* __restri
 // ------------------------------------------------------------------ network gradient ------
 // The gradient of one network (policy or value net) on one minibatch, in two kernels and
 // without a 256 x 256 partial per tile workgroup:
-//   k_vtile   one wave per 16-sample tile, the network's bf16 weights in LDS: forward, loss,
-//             dz2 and dz1 (tanh derivatives from the fp32 activations); db1, db2, dW3, db3
-//             (and d log sigma) and the loss sums per workgroup; q(x) stored as the layer-1
-//             operand, q(dz2) and q(dz1) as half fragments (lane (g, r): feature r of a
-//             16-feature tile, samples 4 g .. 4 g + 3)
-//   k_vwgrad  dW2 = q(dz2) q(h1)^T and dW1 = q(dz1) q(x)^T, a product over the samples, one
-//             partial per chunk of the minibatch; q(h1) recomputed from q(x) with layer 1's
-//             arithmetic, so that it has the forward's bits
-// then k_reduce (and with it the fused Adam step) as for the other gradients.
+//   k_vtile   one wave per 16-sample tile, the network's bf16 weights in LDS: forward, loss and
+//             dz2 (tanh derivatives from the fp32 activations); db2, dW3, db3 (and d log sigma)
+//             and the loss sums per workgroup; q(x) stored as the layer-1 operand, q(dz2) as half
+//             fragments (lane (g, r): feature r of a 16-feature tile, samples 4 g .. 4 g + 3)
+//   k_wgrad   from those two arrays: dh1 = W2^T q(dz2), dz1, dW2 = q(dz2) q(h1)^T and
+//             dW1 = q(dz1) q(x)^T, one partial per chunk of the minibatch; h1 recomputed from
+//             q(x) with layer 1's arithmetic, so that it has the forward's bits
+// then k_reduce (and with it the fused Adam step) as for the other gradients.  With the input
+// gradient in k_vtile, and q(dz1) and (below 131072 samples) q(h1) stored for the second kernel,
+// the value net took 138 + 81 us at 262144 samples, the policy 154 + 81; this way, which reads
+// half of W2 per tile and moves half of the bytes, 85 + 78 and 102 + 78.
 //
 // Layer 1 runs feature-major (D = W1 X: lane (g, r) gets features 4 g + i of an M-tile at
 // sample r, pairs of which are the next layer's operand, as in the rollout).  Layer 2 runs
 // sample-major (D = q(H1)^T W2^T, the layer-1 pairs as the A operand and the W2 fragments as
 // the B operand): lane (g, r) gets z2 feature r of a 16-feature tile at samples 4 g + i, so
 // that the sums over samples of the bias and output-weight gradients are in-lane and the
-// tile's values are already half fragments.  The input gradient dh1 = W2^T q(dz2) is
-// sample-major too, with A = q(dz2) in the feature-major pair layout and B = W2 indexed
-// [z2 feature][h1 feature], which ds_read_b64_tr_b16 reads out of the forward's fragments.
-// A 16 x 16 block changes layout through an MFMA with a 0/1 selection matrix, which is
-// exact (one nonzero product per output).
+// tile's values are already half fragments.  A 16 x 16 block changes layout through an MFMA
+// with a 0/1 selection matrix, which is exact (one nonzero product per output).
 constexpr int VT_WAVES = 8;
-constexpr int VW_WAVES = 8;
-constexpr int VW_MAX_CHUNKS = 128;
+// k_vtile's input gradient (dz1): left to k_wgrad; or formed in it from the tile's own dz2, q(dz1)
+// stored, and without or with q(h1) stored (the value net below VALUE_LATER_STEPS, see k_vwgrad)
+constexpr int DX_LATER = 0, DX_RECOMP = 1, DX_STORE = 2;
+// Steps from which the value net's gradient (in an update of both networks and alone: the two have
+// the same bits) is formed like the policy's.  Below, its input gradient stays in k_vtile: a critic's
+// fit repeats it in a chain of updates, in which another order of its sums grows to a percent of
+// the last gradient's norm (64 updates of 32768 samples), so that the results of a seed would
+// change; k_wgrad would be 6 % faster there.
+constexpr int VALUE_LATER_STEPS = 6144;
 
 struct VtWeights {
   bf16x8 w1[16][64];      // layer 1 A fragments [M-tile][lane] (K = the 32 padded inputs)
@@ -324,7 +329,7 @@ struct VtWeights {
 union VtShared {
   VtWeights s;
   struct {
-    float v[VT_WAVES][3][HID];   // [wave][db1, db2, dW3][feature]
+    float v[VT_WAVES][3][HID];   // [wave][db2, dW3, db1][feature]
     float sc[VT_WAVES][2][4];    // [wave][db3, squared error][lane row g]
   } red;
 };
@@ -344,7 +349,7 @@ struct PtWeights {
 union PtShared {
   PtWeights s;
   struct {
-    float v[VT_WAVES][2][HID];     // [wave][db1, db2][feature]
+    float v[VT_WAVES][HID];        // [wave][feature] db2
     float w3[VT_WAVES][HID][8];    // [wave][feature][output] dW3^T
     float sc[VT_WAVES][2][8];      // [wave][db3, d log sigma][output]
     float st[VT_WAVES][3];         // [wave][surrogate, log-ratio, clipped count]
@@ -360,7 +365,7 @@ __device__ __forceinline__ u32x2 lds_read_tr16(const void* p) {
   return __builtin_bit_cast(u32x2, v);
 }
 
-// LDS slot of lane l's 16 bytes in a W2 fragment: l XOR 4 (l / 16).  The forward reads (16
+// LDS slot of lane l's 16 bytes in a W2 fragment where the input gradient reads it too: l XOR 4 (l / 16).  The forward reads (16
 // lanes at a time, 16 bytes each) stay on distinct banks, and the transposing reads below, whose
 // four source lanes 16 apart address slots 16 apart, no longer all meet on one bank.
 __device__ __forceinline__ int w2_slot(int l) { return l ^ (4 * (l >> 4)); }
@@ -436,13 +441,14 @@ __device__ __forceinline__ u32x2 pack4(const f32x4& v) {
 //                              so that eight accumulators hold all 256 x 8 entries.
 // XP: the value net's pass after the policy's in the same update reads q(x) from x_frag, which
 // the policy's pass wrote for the same tiles, in place of gathering the observations again.
-template <int NOUT, bool H1, bool XP = false>
+template <int NOUT, int DX = DX_LATER, bool XP = false>
 __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __restrict__ w, const float* __restrict__ b,
                                                             const float* __restrict__ log_std, Batch D,
                                                             const int32_t* __restrict__ idx, int B, int tiles, Hp hp,
                                                             Work W) {
   constexpr bool POL = NOUT == 8;
-  static_assert(NOUT == 1 || NOUT == 8, "value net or policy");
+  constexpr bool INGRAD = DX != DX_LATER;
+  static_assert(NOUT == 1 || (NOUT == 8 && !INGRAD), "value net or policy");
   __shared__ std::conditional_t<POL, PtShared, VtShared> U;
   auto& S = U.s;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -500,11 +506,14 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
     }
     return in;
   };
-  int t = blockIdx.x * VT_WAVES + wave;
+  // tiles over the workgroups first, then over their waves (INGRAD: the waves first, which keeps the
+  // order of its sums)
+  int t = INGRAD ? blockIdx.x * VT_WAVES + wave : wave * gridDim.x + blockIdx.x;
   const int stride = gridDim.x * VT_WAVES;
+  auto slot = [](int l) { return INGRAD ? w2_slot(l) : l; };   // LDS slot of a W2 fragment's lane
   In cur = load_in(load_idx(min(t, tiles - 1)));   // in flight while the weights are staged
   {   // weights -> A fragments (lane (g, r) of fragment (M-tile, K tile) holds row 16 mt + r,
-      // inputs 32 kt + kslot(g, j); W2's at slot w2_slot(lane)); every load is issued before
+      // inputs 32 kt + kslot(g, j); W2's at slot(lane)); every load is issued before
       // the first LDS store, so that the loads overlap.  W2 is read in 16-byte pieces of a row
       // (32 consecutive threads per row: every wave load is 1 KiB of two whole rows); the
       // piece of row 16 mt + r at columns 32 kt + o .. + 7 (o = 0, 8, 16, 24) is the half o / 16
@@ -535,8 +544,8 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
       const int e = tid + q * 64 * VT_WAVES, rw = e >> 5, c = 8 * (e & 31);
       const int o = c & 31, g0 = (o & 15) >> 2, rr = rw & 15;
       char* frag = reinterpret_cast<char*>(&S.w2[rw >> 4][c >> 5][0]) + 8 * (o >> 4);
-      *reinterpret_cast<uint2*>(frag + 16 * w2_slot(16 * g0 + rr)) = uint2{v2[q].x, v2[q].y};
-      *reinterpret_cast<uint2*>(frag + 16 * w2_slot(16 * (g0 + 1) + rr)) = uint2{v2[q].z, v2[q].w};
+      *reinterpret_cast<uint2*>(frag + 16 * slot(16 * g0 + rr)) = uint2{v2[q].x, v2[q].y};
+      *reinterpret_cast<uint2*>(frag + 16 * slot(16 * (g0 + 1) + rr)) = uint2{v2[q].z, v2[q].w};
     }
 #pragma unroll
     for (int q = 0; q < P1; ++q) {
@@ -571,8 +580,7 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
     }
   }
   const f32x4 zero = f32x4{0, 0, 0, 0};
-  const int w2s = w2_slot(lane);
-  // db1, db2 and (value net) dW3 of features 16 (4 g + k) + r, k = 0..3 (see rows_reduce_scatter)
+  // db2, (value net) dW3 and (INGRAD) db1 of features 16 (4 g + k) + r, k = 0..3 (see rows_reduce_scatter)
   float sb1[4] = {0, 0, 0, 0}, sb2[4] = {0, 0, 0, 0}, sw3[4] = {0, 0, 0, 0};
   float db3 = 0.0f, sq = 0.0f;
   // policy: dW3^T (lane (g, r): features 16 (2 p + r / 8) + 4 g + i, output r % 8), and per lane
@@ -587,6 +595,11 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
   const float b3 = POL ? 0.0f : b[2 * HID];
 
   for (; t < tiles; t += stride) {
+    // the lane as this tile sees it: the weights in LDS, which no iteration changes, would
+    // otherwise be hoisted out of the loop and spilled
+    int lane_t = tid & 63;
+    if constexpr (!INGRAD) asm volatile("" : "+v"(lane_t));
+    const int lane = lane_t, g = lane >> 4, r = lane & 15;
     const Idx nq = load_idx(min(t + stride, tiles - 1));
     const size_t tb = (size_t)t * 16;
     const bool vr = t * 16 + r < B;
@@ -607,7 +620,7 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
       const f32x4 bb = *reinterpret_cast<const f32x4*>(&S.b1k[32 * kt + 16 + 4 * g]);
       h1[kt] = act_frag(mfma(S.w1[2 * kt][lane], x, zero), mfma(S.w1[2 * kt + 1][lane], x, zero), ba, bb);
     }
-    if (H1) {   // q(h1) as half fragments, for the weight-gradient product of small minibatches
+    if constexpr (DX == DX_STORE) {   // q(h1) as half fragments, for the weight-gradient product of small minibatches
 #pragma unroll
       for (int kt = 0; kt < 8; ++kt) {
         W.h1_half[(tb + 2 * kt) * 64 + lane] = pack4(mfma(h1[kt], select_frag(g, r, 0), zero));
@@ -626,7 +639,7 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
     constexpr int WD = POL ? 4 : 8;
     bf16x8 wf[WD];
 #pragma unroll
-    for (int kt = 0; kt < WD; ++kt) wf[kt] = S.w2[0][kt][w2s];
+    for (int kt = 0; kt < WD; ++kt) wf[kt] = S.w2[0][kt][slot(lane)];
 #pragma unroll
     for (int nt = 0; nt < 16; ++nt) {
       f32x4 acc = zero;
@@ -634,7 +647,7 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
       for (int kt = 0; kt < 8; ++kt) {
         acc = mfma(h1[kt], wf[kt % WD], acc);
         const int nx = 8 * nt + kt + WD;
-        if (nx < 128) wf[kt % WD] = S.w2[nx >> 3][nx & 7][w2s];
+        if (nx < 128) wf[kt % WD] = S.w2[nx >> 3][nx & 7][slot(lane)];
       }
       const float bk = S.b2k[16 * nt + r];
       if constexpr (POL) {
@@ -725,11 +738,17 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
     }
 
     // ---- dz2 = (W3^T q(gy)) (1 - h2^2); db2 (and the value net's dW3) in-lane; q(dz2) as half
-    // fragments and, through the selection MFMA, as the feature-major pairs of the input gradient
-    bf16x8 dzf[8];
+    // fragments.  The next tile's inputs are loaded here, for the policy once half of h2 is dead
+    In nxt;
+    bf16x8 dzf[INGRAD ? 8 : 1];
     float db2[16], dw3[16];
 #pragma unroll
     for (int nt = 0; nt < 16; ++nt) {
+      if (!INGRAD && nt == (POL ? 8 : 0)) {
+        __builtin_amdgcn_sched_barrier(0);
+        nxt = load_in(nq);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       f32x4 dz;
       if constexpr (POL) {
         const u32x2 wt = *reinterpret_cast<const u32x2*>(&S.w3t[16 * nt + r][4 * (g & 1)]);
@@ -750,9 +769,11 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
       db2[nt] = (dz[0] + dz[1]) + (dz[2] + dz[3]);
       const u32x2 q = pack4(dz);
       W.dz2_half[(tb + nt) * 64 + lane] = q;
-      const f32x4 d = mfma(low_half(q), select_frag(g, r, 0), zero);   // features 16 nt + 4 g + i, sample r
+      if constexpr (INGRAD) {
+        const f32x4 d = mfma(low_half(q), select_frag(g, r, 0), zero);   // features 16 nt + 4 g + i, sample r
 #pragma unroll
-      for (int i = 0; i < 4; ++i) dzf[nt >> 1][4 * (nt & 1) + i] = (__bf16)d[i];
+        for (int i = 0; i < 4; ++i) dzf[nt >> 1][4 * (nt & 1) + i] = (__bf16)d[i];
+      }
     }
     {
       float o2[4];
@@ -767,39 +788,41 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
       }
     }
 
-    // ---- dh1 = W2^T q(dz2) sample-major, dz1 = dh1 (1 - h1^2) with h1 recomputed
+    // ---- INGRAD: dh1 = W2^T q(dz2) sample-major, dz1 = dh1 (1 - h1^2) with h1 recomputed
     // sample-major from the inputs, db1 in-lane, q(dz1) as half fragments
-    const In nxt = load_in(nq);
-    // (the transposed fragments are prefetched one feature tile ahead the same way)
-    float db1[16];
-    bf16x8 tf[8];
+    if constexpr (INGRAD) {
+      nxt = load_in(nq);
+      // (the transposed fragments are prefetched one feature tile ahead the same way)
+      float db1[16];
+      bf16x8 tf[8];
 #pragma unroll
-    for (int kt = 0; kt < 8; ++kt) tf[kt] = w2t_frag(S.w2, kt, 0, lane);
+      for (int kt = 0; kt < 8; ++kt) tf[kt] = w2t_frag(S.w2, kt, 0, lane);
 #pragma unroll
-    for (int nt = 0; nt < 16; ++nt) {
-      f32x4 acc = zero;
+      for (int nt = 0; nt < 16; ++nt) {
+        f32x4 acc = zero;
 #pragma unroll
-      for (int kt = 0; kt < 8; ++kt) {
-        acc = mfma(dzf[kt], tf[kt], acc);
-        if (nt + 1 < 16) tf[kt] = w2t_frag(S.w2, kt, nt + 1, lane);
+        for (int kt = 0; kt < 8; ++kt) {
+          acc = mfma(dzf[kt], tf[kt], acc);
+          if (nt + 1 < 16) tf[kt] = w2t_frag(S.w2, kt, nt + 1, lane);
+        }
+        const f32x4 z1 = mfma(x, S.w1[nt][lane], zero);
+        const float bk = S.b1k[16 * nt + r];
+        f32x4 dz;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float h = tanh_bias(z1[i], bk);
+          dz[i] = acc[i] * (1.0f - h * h);
+        }
+        db1[nt] = (dz[0] + dz[1]) + (dz[2] + dz[3]);
+        W.dz1_half[(tb + nt) * 64 + lane] = pack4(dz);
+        __builtin_amdgcn_sched_barrier(0);
       }
-      const f32x4 z1 = mfma(x, S.w1[nt][lane], zero);
-      const float bk = S.b1k[16 * nt + r];
-      f32x4 dz;
+      {
+        float o1[4];
+        rows_reduce_scatter(db1, o1, g);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float h = tanh_bias(z1[i], bk);
-        dz[i] = acc[i] * (1.0f - h * h);
+        for (int k = 0; k < 4; ++k) sb1[k] += o1[k];
       }
-      db1[nt] = (dz[0] + dz[1]) + (dz[2] + dz[3]);
-      W.dz1_half[(tb + nt) * 64 + lane] = pack4(dz);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    {
-      float o1[4];
-      rows_reduce_scatter(db1, o1, g);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) sb1[k] += o1[k];
     }
     cur = nxt;
   }
@@ -811,8 +834,7 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int f = 16 * (4 * g + k) + r;
-      U.red.v[wave][0][f] = sb1[k];
-      U.red.v[wave][1][f] = sb2[k];
+      U.red.v[wave][f] = sb2[k];
     }
 #pragma unroll
     for (int p = 0; p < 8; ++p)
@@ -832,12 +854,11 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
       if (lane == 0) U.red.st[wave][q] = v;
     }
     __syncthreads();
-    for (int o = tid; o < 2 * HID; o += 64 * VT_WAVES) {
-      const int q = o / HID, f = o - q * HID;
+    if (tid < HID) {
       float v = 0.0f;
 #pragma unroll
-      for (int wv = 0; wv < VT_WAVES; ++wv) v += U.red.v[wv][q][f];
-      (q == 0 ? W.part_b1 : W.part_b2)[(size_t)wg * HID + f] = v;
+      for (int wv = 0; wv < VT_WAVES; ++wv) v += U.red.v[wv][tid];
+      W.part_b2[(size_t)wg * HID + tid] = v;
     }
     for (int o = tid; o < 8 * HID; o += 64 * VT_WAVES) {
       const int f = o >> 3, j = o & 7;
@@ -861,23 +882,23 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int f = 16 * (4 * g + k) + r;
-      U.red.v[wave][0][f] = sb1[k];
-      U.red.v[wave][1][f] = sb2[k];
-      U.red.v[wave][2][f] = sw3[k];
+      U.red.v[wave][0][f] = sb2[k];
+      U.red.v[wave][1][f] = sw3[k];
+      if constexpr (INGRAD) U.red.v[wave][2][f] = sb1[k];
     }
     if (r == 0) {
       U.red.sc[wave][0][g] = db3;
       U.red.sc[wave][1][g] = sq;
     }
     __syncthreads();
-    for (int o = tid; o < 3 * HID; o += 64 * VT_WAVES) {
+    for (int o = tid; o < (INGRAD ? 3 : 2) * HID; o += 64 * VT_WAVES) {
       const int q = o / HID, f = o - q * HID;
       float v = 0.0f;
 #pragma unroll
       for (int wv = 0; wv < VT_WAVES; ++wv) v += U.red.v[wv][q][f];
-      if (q == 0)
+      if (q == 2)
         W.part_b1[(size_t)wg * HID + f] = v;
-      else if (q == 1)
+      else if (q == 0)
         W.part_b2[(size_t)wg * HID + f] = v;
       else
         W.part_w3t[((size_t)wg * HID + f) * 16] = v;
@@ -895,6 +916,314 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
   }
 }
 
+// dW2 = q(dz2) q(h1)^T, dz1 = (W2^T q(dz2)) (1 - h1^2), dW1 = q(dz1) q(x)^T and db1 = sum dz1 over
+// the 32-sample steps of one chunk of the minibatch, for one block of COLS = 16 NTW CW hidden-1
+// features (the columns of dW2): workgroup (column block p, chunk c) of eight waves, of which
+// CW = 8 / KP lie side by side across the columns, each owning NTW 16-feature tiles, and KP work
+// on steps of their own (their sums are added at the end).  Per step and wave:
+//   h1 of its features from the stored layer-1 operand q(x), with the forward's products in the
+//     forward's K-slot order (D = q(x) W1^T: lane (g, r) feature r at samples 4 g .. 4 g + 3; the
+//     MFMA gives the same bits with its operands swapped), bias and tanh: fp32 for the
+//     derivative, and rounded as dW2's B operand;
+//   dh1 = q(dz2) W2, sample-major, A = q(dz2) as feature-major pairs, read out of the stored half
+//     fragments with the transposing LDS load, B = the wave's columns of W2, kept in registers
+//     (the second tile's, NTW = 2, in LDS: the accumulators leave no room);
+//   dz1 as dW1's A operand, its B operand q(x) transposed by the same kind of load;
+//   dW2 += q(dz2) q(h1)^T with all 16 row tiles of q(dz2).
+// A step's q(dz2) (16 KB) and q(x) (2 KB) go from memory straight to LDS, NBUF - 1 iterations
+// ahead, with one barrier per iteration.  Every q(dz2) fragment is read from LDS twice per wave,
+// once for each product; more columns per wave take fewer reads, fewer columns per workgroup give
+// small minibatches more workgroups for the same number of chunk partials.
+constexpr int WG_WAVES = 8;
+constexpr int STEP_DZ = 2 * 16 * 64 * 8, STEP_X = 2 * 64 * 16;   // bytes of a step's q(dz2), q(x)
+
+template <int NTW, int KP>
+struct WgPlan {
+  static constexpr int CW = WG_WAVES / KP, COLS = 16 * NTW * CW, NB = HID / COLS;
+  static constexpr int NBUF = NTW == 2 ? 2 : 3;
+  static constexpr bool W2_OVER = NTW == 2;   // W2's rows staged over the step buffers, before them
+};
+template <int NTW, int KP>
+struct WgShared {
+  using P = WgPlan<NTW, KP>;
+  struct Step {
+    char dz[STEP_DZ];   // [feature tile][sample tile][lane] half fragments
+    char x[STEP_X];     // [sample tile][lane] layer-1 operand
+  };
+  union {
+    struct {
+      Step st[P::NBUF][KP];
+      bf16x8 w2t[NTW > 1 ? WG_WAVES : 1][8][64];             // second tile's B fragments of each wave
+    } m;
+    char w2[P::W2_OVER ? HID * P::COLS * 2 : 16];            // W2[:, block] row-major
+    float sum[KP > 1 ? P::CW : 1][KP > 1 ? 64 : 1][76];      // one feature tile's sums of the second half's waves
+  } u;
+  char w2[P::W2_OVER ? 16 : HID * P::COLS * 2];
+};
+
+// 1 KB from memory to LDS: lane l's 16 bytes to dst + 16 l (dst wave-uniform).  Written as
+// assembly: the compiler takes every LDS read as depending on the builtin's loads and waits for
+// all of them, prefetches included.  The program waits for them itself (wait_loads, then a
+// barrier); the assembly writes no register but M0, which this target's other instructions
+// here do not use.
+__device__ __forceinline__ void load_lds(const char* src, char* dst) {
+  const uint32_t off = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)dst;
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(off) : "memory");
+}
+
+template <int N>
+__device__ __forceinline__ void wait_loads() {   // all but the newest N vector memory loads of this wave have landed
+  asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory");
+}
+
+// Barrier of the workgroup's LDS accesses (it does not wait for loads in flight).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+static_assert(sizeof(WgShared<1, 2>) <= 160 * 1024 && sizeof(WgShared<2, 2>) <= 160 * 1024,
+              "weight-gradient kernel LDS exceeds a CU's 160 KB");
+
+template <int NTW, int KP>
+__global__ __launch_bounds__(64 * WG_WAVES, 1) void k_wgrad(const uint16_t* __restrict__ wt, const float* __restrict__ b,
+                                                           Work W, int steps, int chunks) {
+  using P = WgPlan<NTW, KP>;
+  constexpr int CW = P::CW, COLS = P::COLS, NB = P::NB, NBUF = P::NBUF;
+  __shared__ WgShared<NTW, KP> S;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 4, r = lane & 15, tp = lane & 15;
+  const int wc = w % CW, kp = w / CW;
+  // the column blocks of a chunk are workgroups 8 apart, which the dispatcher places on one XCD,
+  // so that their common q(dz2) and q(x) come from its L2
+  const int bid = blockIdx.x, jj = bid >> 3;
+  const int p = jj % NB, c = (jj / NB) * 8 + (bid & 7);
+  const int per = ((steps + chunks - 1) / chunks + KP - 1) / KP * KP;
+  const int u0 = min(steps, c * per), u1 = min(steps, u0 + per);   // whole iterations: steps % 4 == 0
+  const uint16_t* W2 = wt + HID * 23;
+  f32x4 acc[16][NTW], acc1[NTW][2];
+  float sb[NTW];
+#pragma unroll
+  for (int q = 0; q < NTW; ++q) {
+#pragma unroll
+    for (int mt = 0; mt < 16; ++mt) acc[mt][q] = f32x4{0, 0, 0, 0};
+    acc1[q][0] = acc1[q][1] = f32x4{0, 0, 0, 0};
+    sb[q] = 0.0f;
+  }
+  if (u0 < u1) {   // uniform over the workgroup
+    // ---- this wave's loads of iteration `it` (steps u0 + KP it ..), the last one again past it
+    const int iters = (u1 - u0) / KP;
+    constexpr int DPW = KP * 16 / WG_WAVES;   // 1 KB pieces of q(dz2) per wave and iteration; and of
+    const bool has_x = w < 2 * KP;            // q(x), one for each of the first 2 KP waves
+    auto issue = [&](int it, int buf) __attribute__((always_inline)) {
+      const size_t u = (size_t)u0 + (size_t)KP * min(it, iters - 1);
+#pragma unroll
+      for (int q = 0; q < DPW; ++q) {
+        const int k = w * DPW + q;   // feature tile k % 16 of step k / 16: 32 lanes per sample tile
+        load_lds((const char*)W.dz2_half + (u + k / 16) * STEP_DZ + (k % 16) * 512 + 16 * lane + (lane >> 5) * (STEP_DZ / 2 - 512),
+                 S.u.m.st[buf][k / 16].dz + (k % 16) * 1024);
+      }
+      if (has_x)
+        load_lds((const char*)W.x_frag + (u + (w >> 1)) * STEP_X + (w & 1) * 1024 + 16 * lane,
+                 S.u.m.st[buf][w >> 1].x + (w & 1) * 1024);
+    };
+    // ---- weights: W2's columns of this block, row-major, and from them the wave's B fragments
+    char* w2s = P::W2_OVER ? S.u.w2 : S.w2;
+    constexpr int LPR = COLS * 2 / 16, RPI = 64 / LPR;   // lanes per row piece, rows per load
+    {
+      const char* src = (const char*)(W2 + COLS * p) + 16 * (lane % LPR) + (size_t)(lane / LPR) * (HID * 2);
+#pragma unroll
+      for (int q = 0; q < HID / RPI / WG_WAVES; ++q) {
+        const int k = w * (HID / RPI / WG_WAVES) + q;
+        load_lds(src + (size_t)k * RPI * (HID * 2), w2s + k * 1024);
+      }
+    }
+    if (!P::W2_OVER)
+#pragma unroll
+      for (int j = 0; j < NBUF - 1; ++j) issue(j, j);
+    bf16x8 w1f[NTW];   // layer 1: lane (g, r) = W1[f][kslot(g, j)] of its feature f = f0 + 16 q + r
+    float b1k[NTW];
+    const int f0 = COLS * p + 16 * NTW * wc;
+#pragma unroll
+    for (int q = 0; q < NTW; ++q) {
+      const int f = f0 + 16 * q + r;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int k = kslot(g, j);
+        const uint16_t v = wt[f * 23 + min(k, 22)];
+        w1f[q][j] = bf16_of_bits(k < 23 ? v : (uint16_t)0);
+      }
+      b1k[q] = b[f] * TWO_LOG2E;
+    }
+    wait_loads<0>();
+    lds_barrier();
+    // B fragment (kt, q): lane (g, r) slot 4 h + e = W2[32 kt + 16 h + 4 g + e][f0 + 16 q + r]; the
+    // source lane 4 e + a of row g addresses columns 4 a .. + 3 of that row
+    bf16x8 w2t[8], w2t1[NTW > 1 ? 8 : 1];
+    auto w2_frag = [&](int kt, int q) __attribute__((always_inline)) {
+      const char* a0 = w2s + (32 * kt + 4 * g + (tp >> 2)) * (COLS * 2) + 2 * (16 * (NTW * wc + q) + 4 * (tp & 3));
+      return join(lds_read_tr16(a0), lds_read_tr16(a0 + 16 * COLS * 2));
+    };
+#pragma unroll
+    for (int kt = 0; kt < 8; ++kt) {
+      w2t[kt] = w2_frag(kt, 0);
+      if constexpr (NTW > 1) w2t1[kt] = w2_frag(kt, 1);
+    }
+    if (P::W2_OVER) {
+      lds_barrier();   // every wave has read the rows that the step buffers overwrite
+      if constexpr (NTW > 1) {
+#pragma unroll
+        for (int kt = 0; kt < 8; ++kt) S.u.m.w2t[w][kt][lane] = w2t1[kt];
+      }
+#pragma unroll
+      for (int j = 0; j < NBUF - 1; ++j) issue(j, j);
+    }
+    // per-lane offsets of the transposing reads: q(dz2) pairs and q(x)
+    const int tr_dz = (16 * (tp & 3) + 4 * g + (tp >> 2)) * 8, tr_x = (16 * (tp & 3) + 4 * g + (tp >> 2)) * 16;
+    const f32x4 zero = f32x4{0, 0, 0, 0};
+    for (int it = 0; it < iters; ++it) {
+      if (has_x)
+        wait_loads<(NBUF - 2) * (DPW + 1)>();
+      else
+        wait_loads<(NBUF - 2) * DPW>();
+      lds_barrier();   // every wave's loads of this iteration are in LDS, its reads of the one before done
+      issue(it + NBUF - 1, (it + NBUF - 1) % NBUF);
+      const char* dz = S.u.m.st[it % NBUF][kp].dz;
+      const char* xs = S.u.m.st[it % NBUF][kp].x;
+      // dh1 of this wave's features
+      f32x4 d[NTW][2];
+#pragma unroll
+      for (int q = 0; q < NTW; ++q) d[q][0] = d[q][1] = zero;
+#pragma unroll
+      for (int kt = 0; kt < 8; ++kt) {
+        bf16x8 wb = w2t[kt];
+        bf16x8 wb1 = NTW > 1 ? S.u.m.w2t[NTW > 1 ? w : 0][kt][lane] : wb;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const char* a0 = dz + 2 * kt * 1024 + t * 512 + tr_dz;
+          const bf16x8 A = join(lds_read_tr16(a0), lds_read_tr16(a0 + 1024));
+          d[0][t] = mfma(A, wb, d[0][t]);
+          if constexpr (NTW > 1) d[1][t] = mfma(A, wb1, d[1][t]);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);   // h1 after dh1: their registers are not live together
+      // h1 of this wave's features
+      f32x4 h[NTW][2];
+      bf16x8 hf[NTW];
+      {
+        const bf16x8 xa[2] = {*reinterpret_cast<const bf16x8*>(xs + 16 * lane),
+                              *reinterpret_cast<const bf16x8*>(xs + 1024 + 16 * lane)};
+#pragma unroll
+        for (int q = 0; q < NTW; ++q) {
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            const f32x4 z = mfma(xa[t], w1f[q], zero);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) h[q][t][i] = tanh_bias(z[i], b1k[q]);
+          }
+          hf[q] = join(pack4(h[q][0]), pack4(h[q][1]));
+        }
+      }
+      // dz1, db1, dW1
+      bf16x8 xb[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        xb[k] = join(lds_read_tr16(xs + tr_x + 8 * k), lds_read_tr16(xs + 1024 + tr_x + 8 * k));
+#pragma unroll
+      for (int q = 0; q < NTW; ++q) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) d[q][t][i] *= 1.0f - h[q][t][i] * h[q][t][i];
+          sb[q] += (d[q][t][0] + d[q][t][1]) + (d[q][t][2] + d[q][t][3]);
+        }
+        const bf16x8 e = join(pack4(d[q][0]), pack4(d[q][1]));
+#pragma unroll
+        for (int k = 0; k < 2; ++k) acc1[q][k] = mfma(e, xb[k], acc1[q][k]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      // dW2
+#pragma unroll
+      for (int mt = 0; mt < 16; ++mt) {
+        const bf16x8 A = join(*reinterpret_cast<const u32x2*>(dz + mt * 1024 + 8 * lane),
+                              *reinterpret_cast<const u32x2*>(dz + mt * 1024 + 512 + 8 * lane));
+#pragma unroll
+        for (int q = 0; q < NTW; ++q) acc[mt][q] = mfma(A, hf[q], acc[mt][q]);
+      }
+    }
+    wait_loads<0>();   // those issued past the end too
+    lds_barrier();     // every wave is done with the step buffers
+  }
+  // ---- the chunk's partials
+  if constexpr (KP > 1) {   // add the other half's sums, tile by tile, in a fixed order
+    float* mine = &S.u.sum[wc][lane][0];
+#pragma unroll
+    for (int q = 0; q < NTW; ++q) {
+      if (kp == 1) {
+#pragma unroll
+        for (int mt = 0; mt < 16; ++mt) *reinterpret_cast<f32x4*>(mine + 4 * mt) = acc[mt][q];
+        *reinterpret_cast<f32x4*>(mine + 64) = acc1[q][0];
+        *reinterpret_cast<f32x4*>(mine + 68) = acc1[q][1];
+        mine[72] = sb[q];
+      }
+      __syncthreads();
+      if (kp == 0) {
+#pragma unroll
+        for (int mt = 0; mt < 16; ++mt) acc[mt][q] += *reinterpret_cast<const f32x4*>(mine + 4 * mt);
+        acc1[q][0] += *reinterpret_cast<const f32x4*>(mine + 64);
+        acc1[q][1] += *reinterpret_cast<const f32x4*>(mine + 68);
+        sb[q] += mine[72];
+      }
+      __syncthreads();
+    }
+    if (kp == 1) return;
+  }
+  float* o2 = W.part_w2 + (size_t)c * HID * HID;
+  float* o1 = W.part_w1 + (size_t)c * HID * 32;
+#pragma unroll
+  for (int q = 0; q < NTW; ++q) {
+    const int f = COLS * p + 16 * (NTW * wc + q);
+#pragma unroll
+    for (int mt = 0; mt < 16; ++mt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o2[(16 * mt + 4 * g + i) * HID + f + r] = acc[mt][q][i];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o1[(f + 4 * g + i) * 32 + 16 * k + r] = acc1[q][k][i];
+    float v = sb[q];   // lane (g, r): samples 4 g .. + 3 of every tile
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    if (g == 0) W.part_b1[(size_t)c * HID + f + r] = v;
+  }
+}
+
+// Workgroups of k_vtile.  Half of the waves of a workgroup (one per SIMD) have a tile while that
+// takes at most half of the CUs: 3000 samples 72 us per update against 76 with every wave, but
+// at 16384 samples, where it would take all CUs to stage the weights, 110 against 104.
+inline int vt_groups(int tiles, int cus) {
+  return std::min(cus, std::max((tiles + VT_WAVES - 1) / VT_WAVES, std::min((tiles + 3) / 4, cus / 2)));
+}
+
+// Shape of the weight-gradient product by the minibatch's 32-sample steps.  From 6144 steps
+// (196608 samples) 128-column blocks of two tiles per wave, 128 chunks, 256 workgroups: an
+// update of 262144 samples takes 390 us, with 64-column blocks (one tile per wave, twice the LDS
+// reads per column) 416, with 256-column blocks (256 chunk partials, 64 MB) 419.  Below, 64-column
+// blocks of 8 to 64 chunks of eight steps or more, which have four workgroups per chunk: 131072
+// samples 244 us against 252, 32768 121 against 136; at 3000 samples chunks of eight steps take
+// 76 us per update, of 16 82.
+struct VwPlan {
+  int cols, chunks;
+};
+inline VwPlan vw_plan(int steps) {
+  if (steps >= VALUE_LATER_STEPS) return {128, 128};
+  const int c = (steps / 8 + 7) / 8 * 8;
+  return {64, c < 8 ? 8 : (c > 64 ? 64 : c)};
+}
+
+// The value net's product below VALUE_LATER_STEPS, from stored q(dz2), q(dz1) and q(x):
 // dW2 = q(dz2) q(h1)^T and dW1 = q(dz1) q(x)^T over the 32-sample steps of one chunk of the
 // minibatch, for one block of ROWS (64 or 128) gradient rows: workgroup (row block p, chunk
 // c), eight waves; wave w accumulates rows ROWS p .. + ROWS - 1 x dW2 columns 32 w .. + 31
@@ -918,11 +1247,11 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
 // minibatches the recomputation in four row blocks costs more than the loads it saves.
 // `chunks` is a multiple of 8; grid = (256 / ROWS) chunks.
 template <int ROWS, bool RECOMP>
-__global__ __launch_bounds__(64 * VW_WAVES, 1) void k_vwgrad(const uint16_t* __restrict__ w1, const float* __restrict__ b,
+__global__ __launch_bounds__(64 * WG_WAVES, 1) void k_vwgrad(const uint16_t* __restrict__ w1, const float* __restrict__ b,
                                                             Work W, int steps, int chunks) {
   constexpr int MT = ROWS / 16;              // row tiles of the block
   constexpr int NB = HID / ROWS;             // row blocks of a chunk
-  constexpr int SPW = 2 * MT / VW_WAVES;     // q(dz2) / q(dz1) row tiles staged by each wave
+  constexpr int SPW = 2 * MT / WG_WAVES;     // q(dz2) / q(dz1) row tiles staged by each wave
   constexpr int DEPTH = ROWS == 64 ? 8 : 4;  // steps of loads in flight (register ring)
   __shared__ bf16x8 Ad[2][MT][64];   // q(dz2) A fragments: rows ROWS p + 16 mt
   __shared__ bf16x8 A1[2][MT][64];   // q(dz1) A fragments: rows ROWS p + 16 mt
@@ -968,7 +1297,7 @@ __global__ __launch_bounds__(64 * VW_WAVES, 1) void k_vwgrad(const uint16_t* __r
       u = min(u, u1 - 1);
 #pragma unroll
       for (int q = 0; q < SPW; ++q) {
-        const int k = w + VW_WAVES * q;
+        const int k = w + WG_WAVES * q;
         const u32x2* sa = k < MT ? W.dz2_half : W.dz1_half;
         const int smt = MT * p + k % MT;
         R.a[q] = join(sa[at(2 * u, smt, 16)], sa[at(2 * u + 1, smt, 16)]);
@@ -1016,7 +1345,7 @@ __global__ __launch_bounds__(64 * VW_WAVES, 1) void k_vwgrad(const uint16_t* __r
           }
 #pragma unroll
           for (int q = 0; q < SPW; ++q) {
-            const int k = w + VW_WAVES * q;
+            const int k = w + WG_WAVES * q;
             if (k < MT)
               Ad[buf][k][lane] = R[j].a[q];
             else
@@ -1039,7 +1368,7 @@ __global__ __launch_bounds__(64 * VW_WAVES, 1) void k_vwgrad(const uint16_t* __r
           }
 #pragma unroll
           for (int q = 0; q < SPW; ++q) {
-            const int k = w + VW_WAVES * q;
+            const int k = w + WG_WAVES * q;
             acc1[q] = mfma(A1[buf][k % MT][lane], Xb[buf][k / MT][lane], acc1[q]);
           }
         }
@@ -1057,24 +1386,24 @@ __global__ __launch_bounds__(64 * VW_WAVES, 1) void k_vwgrad(const uint16_t* __r
   float* o1 = W.part_w1 + (size_t)c * HID * 32;
 #pragma unroll
   for (int q = 0; q < SPW; ++q) {
-    const int k = w + VW_WAVES * q;
+    const int k = w + WG_WAVES * q;
 #pragma unroll
     for (int i = 0; i < 4; ++i) o1[(ROWS * p + 16 * (k % MT) + 4 * g + i) * 32 + 16 * (k / MT) + r] = acc1[q][i];
   }
 }
 
-// Chunks of the weight-gradient product and its row-block height: from VW_RECOMP_STEPS
+// Chunks of that product and its row-block height: from VW_RECOMP_STEPS
 // steps of 32 samples up, 128-row blocks with q(h1) recomputed and about one chunk per 64
 // steps (up to 128 chunks, 256 workgroups); below that, 64-row blocks reading the stored
 // q(h1) and about one chunk per 16 steps (8 to 64 chunks), which keeps the chunk partials
 // small against the data at the small sizes.
-struct VwPlan {
+struct VwRows {
   int rows, chunks;
 };
-inline VwPlan vw_plan(int steps) {
+inline VwRows vw_rows(int steps) {
   if (steps >= VW_RECOMP_STEPS) {
     const int c = (steps / 64 + 7) / 8 * 8;
-    return {128, c > VW_MAX_CHUNKS ? VW_MAX_CHUNKS : c};
+    return {128, c > 128 ? 128 : c};
   }
   const int c = (steps / 16 + 7) / 8 * 8;
   return {64, c < 8 ? 8 : (c > 64 ? 64 : c)};
@@ -1346,45 +1675,50 @@ static int grad_launch(const auv_ppo_config* cfg, const auv_mlp* policy, const a
   const int rb = ppo::red_blocks(ACT);
   // per network: the per-tile kernel (GV workgroups of VT_WAVES waves) and the weight-gradient
   // product (chunk partials), then the reduce of both kinds of partials
-  const int GV = std::min(cus, (tiles + ppo::VT_WAVES - 1) / ppo::VT_WAVES);
+  // k_vtile and the weight-gradient product of each network (see VALUE_LATER_STEPS for the value net)
+  const bool later = steps >= ppo::VALUE_LATER_STEPS;
   const ppo::VwPlan vp = ppo::vw_plan(steps);
-  const int chunks = vp.chunks;
-  const dim3 vt_block(64 * ppo::VT_WAVES), vw_block(64 * ppo::VW_WAVES);
-  // xp: the value net's pass takes q(x) from the policy's pass instead of gathering it again
-  auto tile_grad = [&](const auv_mlp* net, bool pol, bool xp) {
-    const float* ls = pol ? net->log_std : nullptr;
-    if (vp.rows == 128) {
-      if (pol)
-        hipLaunchKernelGGL((ppo::k_vtile<8, false>), dim3(GV), vt_block, 0, s, net->w, net->b, ls, D, idx, B, tiles, hp, W);
-      else if (xp)
-        hipLaunchKernelGGL((ppo::k_vtile<1, false, true>), dim3(GV), vt_block, 0, s, net->w, net->b, ls, D, idx, B, tiles, hp, W);
-      else
-        hipLaunchKernelGGL((ppo::k_vtile<1, false>), dim3(GV), vt_block, 0, s, net->w, net->b, ls, D, idx, B, tiles, hp, W);
-      hipLaunchKernelGGL((ppo::k_vwgrad<128, true>), dim3(2 * chunks), vw_block, 0, s, net->w, net->b, W, steps, chunks);
-    } else {
-      if (pol)
-        hipLaunchKernelGGL((ppo::k_vtile<8, true>), dim3(GV), vt_block, 0, s, net->w, net->b, ls, D, idx, B, tiles, hp, W);
-      else if (xp)
-        hipLaunchKernelGGL((ppo::k_vtile<1, true, true>), dim3(GV), vt_block, 0, s, net->w, net->b, ls, D, idx, B, tiles, hp, W);
-      else
-        hipLaunchKernelGGL((ppo::k_vtile<1, true>), dim3(GV), vt_block, 0, s, net->w, net->b, ls, D, idx, B, tiles, hp, W);
-      hipLaunchKernelGGL((ppo::k_vwgrad<64, false>), dim3(4 * chunks), vw_block, 0, s, net->w, net->b, W, steps, chunks);
-    }
+  const ppo::VwRows vr = ppo::vw_rows(steps);
+  const int GP = ppo::vt_groups(tiles, cus);
+  const int GV = later ? GP : std::min(cus, (tiles + ppo::VT_WAVES - 1) / ppo::VT_WAVES);
+  const int chunks_v = later ? vp.chunks : vr.chunks;
+  const dim3 vt_block(64 * ppo::VT_WAVES), vw_block(64 * ppo::WG_WAVES);
+  auto tiles_of = [&](auto kernel, int G, const auv_mlp* net) {
+    hipLaunchKernelGGL(kernel, dim3(G), vt_block, 0, s, net->w, net->b, net->log_std, D, idx, B, tiles, hp, W);
+  };
+  auto product = [&](const auv_mlp* net) {
+    const dim3 grid(HID / vp.cols * vp.chunks);
+    if (vp.cols == 128)
+      hipLaunchKernelGGL((ppo::k_wgrad<2, 2>), grid, vw_block, 0, s, net->w, net->b, W, steps, vp.chunks);
+    else
+      hipLaunchKernelGGL((ppo::k_wgrad<1, 2>), grid, vw_block, 0, s, net->w, net->b, W, steps, vp.chunks);
   };
   if (with_policy) {
     if (hp.normalize) {
       hipLaunchKernelGGL(ppo::k_adv_partial, dim3(ppo::ADV_BLOCKS), dim3(256), 0, s, batch->adv, idx, B, (int)batch->M,
                          W.adv_part);
     }
-    tile_grad(policy, true, false);
-    hipLaunchKernelGGL(ppo::k_reduce, dim3(rb), dim3(256), 0, s, ACT, hp.n_act, GV, chunks, GV, chunks, W, cfg->ent_coef,
-                       grad_policy, W.part_ss, ppo::AdamFuse{});
+    tiles_of(ppo::k_vtile<8>, GP, policy);
+    product(policy);
+    hipLaunchKernelGGL(ppo::k_reduce, dim3(rb), dim3(256), 0, s, ACT, hp.n_act, GP, vp.chunks, vp.chunks, vp.chunks, W,
+                       cfg->ent_coef, grad_policy, W.part_ss, ppo::AdamFuse{});
   }
-  tile_grad(value, false, with_policy);
-  hipLaunchKernelGGL(ppo::k_reduce, dim3(ppo::red_blocks(1)), dim3(256), 0, s, 1, 1, GV, chunks, GV, chunks, W, 0.0f,
-                     grad_value, W.part_ss + rb, fuse);
+  // the value net's pass takes q(x) from the policy's where there is one
+  using namespace ppo;
+  if (later) {
+    tiles_of(with_policy ? k_vtile<1, DX_LATER, true> : k_vtile<1, DX_LATER, false>, GV, value);
+    product(value);
+  } else if (vr.rows == 128) {
+    tiles_of(with_policy ? k_vtile<1, DX_RECOMP, true> : k_vtile<1, DX_RECOMP, false>, GV, value);
+    hipLaunchKernelGGL((k_vwgrad<128, true>), dim3(2 * chunks_v), vw_block, 0, s, value->w, value->b, W, steps, chunks_v);
+  } else {
+    tiles_of(with_policy ? k_vtile<1, DX_STORE, true> : k_vtile<1, DX_STORE, false>, GV, value);
+    hipLaunchKernelGGL((k_vwgrad<64, false>), dim3(4 * chunks_v), vw_block, 0, s, value->w, value->b, W, steps, chunks_v);
+  }
+  hipLaunchKernelGGL(ppo::k_reduce, dim3(ppo::red_blocks(1)), dim3(256), 0, s, 1, 1, GV, chunks_v, later ? chunks_v : GV,
+                     chunks_v, W, 0.0f, grad_value, W.part_ss + rb, fuse);
   if (finalize)
-    hipLaunchKernelGGL(ppo::k_finalize, dim3(1), dim3(256), 0, s, with_policy ? GV : 0, GV, W, with_policy ? rb : 0,
+    hipLaunchKernelGGL(ppo::k_finalize, dim3(1), dim3(256), 0, s, with_policy ? GP : 0, GV, W, with_policy ? rb : 0,
                        ppo::red_blocks(1), rb, with_policy ? policy->log_std : (const float*)nullptr, hp, stats);
   return check_launch("auv_ppo_grad");
 }

@@ -429,3 +429,37 @@ def test_ppo_learns_the_paper_task():
     assert r[0] < -20.0, r[0]
     assert r[-1] > 0.1 * r[0] and r[-1] > -10.0, r[-1]
     assert np.mean(r[-10:]) > np.mean(r[:10]) + 20.0
+
+
+@pytest.mark.parametrize("B", [96, 128 * 9 - 16, 65536, 98304])
+def test_ppo_grad_of_a_doubled_minibatch(B):
+    """Every sample of a minibatch twice has the minibatch's own gradients: the weight 1/B is
+    halved exactly, so every bf16 operand keeps its bits (scaled by two) and only the order of
+    the fp32 sums differs.  98304 samples are 3072 steps of the weight-gradient product and
+    196608 the 6144 at which its shape changes; 96 and 1136 leave chunks and half of the waves
+    without steps.  Bound: a fixed-order fp32 sum over 2 B terms of random sign, relative to the
+    largest entry of the block."""
+    from paper_2512_13359_amd import PpoLearner
+    announce(f"PPO doubled minibatch B={B}")
+    require_gpu()
+    M = 100000
+    r = np.random.default_rng(B)
+    dev = lambda x: torch.from_numpy(np.asarray(x, np.float32)).cuda()  # noqa: E731
+    L = PpoLearner(W.mlp_weights(8, W.POLICY_SEED), W.mlp_weights(1, W.VALUE_SEED), normalize_adv=False)
+    bufs = (dev(r.uniform(-1.5, 1.5, (23, M))), dev(r.normal(0, 0.8, (8, M))), dev(r.uniform(-9, -6, M)),
+            dev(r.standard_normal(M)), dev(r.standard_normal(M)))
+    batch = L.batch(*bufs)
+    idx = torch.from_numpy(r.permutation(M)[:B].astype(np.int32)).cuda()
+
+    def grads(ix):
+        for n in (L.pol, L.val):
+            n.grad.fill_(float("nan"))
+        L.grad(batch, ix)
+        return L.pol.grad.double(), L.val.grad.double()
+
+    for n_out, one, two in zip((8, 1), grads(idx), grads(torch.cat([idx, idx]))):
+        assert torch.isfinite(one).all()
+        nw1, nw12, nw = 256 * 23, 256 * 23 + 256 * 256, 256 * 23 + 256 * 256 + 256 * n_out
+        for lo, hi in ((0, nw1), (nw1, nw12), (nw12, nw), (nw, nw + 256), (nw + 256, nw + 512), (nw + 512, one.numel())):
+            a, b = one[lo:hi], two[lo:hi]
+            assert (a - b).abs().max() <= 4 * 2.0 ** -24 * np.sqrt(2 * B) * a.abs().max(), (n_out, lo, hi)
