@@ -400,8 +400,6 @@ constexpr int MLPW_NT = 2;   // 16-sample tiles per wave and group
 // 13.5 us; fewer than four gained nothing, the weights' staging being the rest).
 constexpr int MLPW_SHARE = 4;
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
 struct MlpWideShared {
   bf16x8 w1[16][64];      // layer 1 [M-tile][lane] (K = the 32 padded inputs)
   bf16x8 w2[16][8][64];   // layer 2 [M-tile][K step][lane]
@@ -420,28 +418,13 @@ __global__ __launch_bounds__(64 * MLPW_WAVES, 2) void k_mlp(const uint16_t* __re
   const int g = lane >> 4, r = lane & 15;
   {   // weights -> A fragments: lane (g, r) of fragment (M-tile mt, K step kt) holds row
       // 16 mt + r, inputs 32 kt + kslot(g, j)
-    const uint16_t* W1 = w;
-    const uint16_t* W2 = w + HID * 23;
-    const uint16_t* W3 = W2 + HID * HID;
+    const uint16_t* W3 = w + HID * 23 + HID * HID;
     // Every load is issued before the first LDS store, so that a workgroup waits for memory once
     // (a loop of load-then-store over the fragments waited 19 times: 20 us of the kernel at any
-    // size).  W2 is read in 16-byte pieces of whole rows; the piece of row 16 mt + r at columns
-    // 32 kt + o .. + 7 (o = 0, 8, 16, 24) is the half o / 16 (K slots 4 (o / 16) .. + 3) of lanes
-    // 16 g + r and 16 (g + 1) + r, g = (o % 16) / 4.
-    constexpr int NT = 64 * MLPW_WAVES, P2 = HID * HID / 8 / NT, P1 = 16 * 64 / NT;
-    u32x4 v2[P2];
-    uint16_t v1[P1][8], v3[8];
-#pragma unroll
-    for (int q = 0; q < P2; ++q) {
-      const int e = tid + q * NT;
-      v2[q] = *reinterpret_cast<const u32x4*>(W2 + (e >> 5) * HID + 8 * (e & 31));
-    }
-#pragma unroll
-    for (int q = 0; q < P1; ++q) {
-      const int e = tid + q * NT, f = e >> 6, l = e & 63;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v1[q][j] = W1[(16 * f + (l & 15)) * 23 + min(kslot(l >> 4, j), 22)];
-    }
+    // size).
+    StageWeights<MLPW_WAVES> st;
+    st.load(w, w + HID * 23, wave, lane);
+    uint16_t v3[8];
     const int k3 = tid >> 6, g3 = (tid >> 4) & 3, r3 = tid & 15;   // one layer-3 slot per thread
     {
       const uint16_t* p = W3 + min(r3, n_out - 1) * HID + 32 * k3 + 4 * g3;
@@ -449,22 +432,7 @@ __global__ __launch_bounds__(64 * MLPW_WAVES, 2) void k_mlp(const uint16_t* __re
       for (int j = 0; j < 8; ++j) v3[j] = p[16 * (j >> 2) + (j & 3)];
     }
     const float bb1 = b[tid & (HID - 1)], bb2 = b[HID + (tid & (HID - 1))], bb3 = b[2 * HID + min(tid, n_out - 1)];
-#pragma unroll
-    for (int q = 0; q < P2; ++q) {
-      const int e = tid + q * NT, rw = e >> 5, c = 8 * (e & 31);
-      const int o = c & 31, g0 = (o & 15) >> 2, rr = rw & 15;
-      char* frag = reinterpret_cast<char*>(&S.w2[rw >> 4][c >> 5][0]) + 8 * (o >> 4);
-      *reinterpret_cast<uint2*>(frag + 16 * (16 * g0 + rr)) = uint2{v2[q].x, v2[q].y};
-      *reinterpret_cast<uint2*>(frag + 16 * (16 * (g0 + 1) + rr)) = uint2{v2[q].z, v2[q].w};
-    }
-#pragma unroll
-    for (int q = 0; q < P1; ++q) {
-      const int e = tid + q * NT, f = e >> 6, l = e & 63;
-      bf16x8 v;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = bf16_of_bits(kslot(l >> 4, j) < 23 ? v1[q][j] : (uint16_t)0);
-      S.w1[f][l] = v;
-    }
+    st.store(S.w1, S.w2, wave, lane, [](int l) { return l; });
     {
       bf16x8 v;
 #pragma unroll

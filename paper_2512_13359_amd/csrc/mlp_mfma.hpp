@@ -53,4 +53,53 @@ __device__ __forceinline__ bf16x8 act_frag(const f32x4& d0, const f32x4& d1, con
   return f;
 }
 
+// A workgroup's copy of W1 and W2 (row-major in memory) into LDS as MFMA A fragments: lane (g, r) of
+// fragment (M-tile mt, K tile kt) holds row 16 mt + r, inputs 32 kt + kslot(g, j), W2's at slot(lane)
+// of its fragment.  load() issues every load, store() writes LDS, so that a kernel can issue its
+// other loads in between and wait for memory once.  W2 is read in 16-byte pieces of a row; the
+// piece of row 16 mt + r at columns 32 kt + o .. + 7 (o = 0, 8, 16, 24) is the half o / 16 (K slots
+// 4 (o / 16) .. + 3) of lanes 16 g + r and 16 (g + 1) + r, g = (o % 16) / 4.  A wave's load takes 128
+// bytes of each of eight rows: its stores then meet on a bank at most four at a time (with two whole
+// rows per load sixteen at a time, 3 us of every launch that stages the weights).
+template <int WAVES>
+struct StageWeights {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  static constexpr int P2 = HID * HID / 8 / (64 * WAVES), P1 = 16 / WAVES;
+  u32x4 v2[P2];
+  uint16_t v1[P1][8];
+
+  __device__ __forceinline__ static int row(int q, int wave, int lane) { return 8 * ((q * WAVES + wave) >> 2) + (lane >> 3); }
+  __device__ __forceinline__ static int col(int q, int wave, int lane) {
+    return 64 * ((q * WAVES + wave) & 3) + 8 * (lane & 7);
+  }
+  __device__ __forceinline__ void load(const uint16_t* __restrict__ w1, const uint16_t* __restrict__ w2, int wave,
+                                       int lane) {
+#pragma unroll
+    for (int q = 0; q < P2; ++q)
+      v2[q] = *reinterpret_cast<const u32x4*>(w2 + row(q, wave, lane) * HID + col(q, wave, lane));
+#pragma unroll
+    for (int q = 0; q < P1; ++q)
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        v1[q][j] = w1[(16 * (q * WAVES + wave) + (lane & 15)) * 23 + min(kslot(lane >> 4, j), 22)];
+  }
+  template <class Slot>
+  __device__ __forceinline__ void store(bf16x8 (*w1)[64], bf16x8 (*w2)[8][64], int wave, int lane, Slot slot) const {
+#pragma unroll
+    for (int q = 0; q < P2; ++q) {
+      const int rw = row(q, wave, lane), c = col(q, wave, lane), o = c & 31, g0 = (o & 15) >> 2, rr = rw & 15;
+      char* frag = reinterpret_cast<char*>(&w2[rw >> 4][c >> 5][0]) + 8 * (o >> 4);
+      *reinterpret_cast<uint2*>(frag + 16 * slot(16 * g0 + rr)) = uint2{v2[q].x, v2[q].y};
+      *reinterpret_cast<uint2*>(frag + 16 * slot(16 * (g0 + 1) + rr)) = uint2{v2[q].z, v2[q].w};
+    }
+#pragma unroll
+    for (int q = 0; q < P1; ++q) {
+      bf16x8 v;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = bf16_of_bits(kslot(lane >> 4, j) < 23 ? v1[q][j] : (uint16_t)0);
+      w1[q * WAVES + wave][lane] = v;
+    }
+  }
+};
+
 }  // namespace auv

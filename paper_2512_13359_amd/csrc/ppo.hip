@@ -340,7 +340,7 @@ struct PtWeights {
   bf16x8 w1[16][64];
   bf16x8 w2[16][8][64];
   bf16x8 w3a[8][32];      // output-layer A fragments [K tile][8 g + output]: W3[o][32 kt + kslot(g, j)]
-  uint16_t w3t[HID][8];   // W3 transposed [feature][output] (the input-gradient operand)
+  alignas(16) uint16_t w3t[HID][8];   // W3 transposed [feature][output] (the input-gradient operand)
   float b1k[HID];
   float b2k[HID];
   float b3[8];
@@ -512,71 +512,40 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
   const int stride = gridDim.x * VT_WAVES;
   auto slot = [](int l) { return INGRAD ? w2_slot(l) : l; };   // LDS slot of a W2 fragment's lane
   In cur = load_in(load_idx(min(t, tiles - 1)));   // in flight while the weights are staged
-  {   // weights -> A fragments (lane (g, r) of fragment (M-tile, K tile) holds row 16 mt + r,
-      // inputs 32 kt + kslot(g, j); W2's at slot(lane)); every load is issued before
-      // the first LDS store, so that the loads overlap.  W2 is read in 16-byte pieces of a row
-      // (32 consecutive threads per row: every wave load is 1 KiB of two whole rows); the
-      // piece of row 16 mt + r at columns 32 kt + o .. + 7 (o = 0, 8, 16, 24) is the half o / 16
-      // (K slots 4 (o / 16) .. + 3) of lanes 16 g + r and 16 (g + 1) + r, g = (o % 16) / 4.
-    const uint16_t* W1 = w;
-    const uint16_t* W2 = w + HID * 23;
-    const uint16_t* W3 = W2 + HID * HID;
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr int P2 = HID * HID / 8 / (64 * VT_WAVES), P1 = 16 * 64 / (64 * VT_WAVES);
-    u32x4 v2[P2];
-    uint16_t v1[P1][8];
+  const float b3 = POL ? 0.0f : b[2 * HID];
+  {   // weights and biases to LDS, every load issued before the first LDS store
+    const uint16_t* W3 = w + HID * 23 + HID * HID;
+    StageWeights<VT_WAVES> st;
+    st.load(w, w + HID * 23, wave, lane);
+    const int f = tid & (HID - 1);
+    const float vb1 = b[f], vb2 = b[HID + f];
+    if constexpr (POL) {
+      // W3[o][f] at W3[o * HID + f].  Threads 0 .. 255: one output-layer fragment slot (K tile tid / 32,
+      // lane row (tid / 8) % 4, output tid % 8); threads 256 .. 511: the eight outputs of feature f
+      const bool frag = tid < HID;
+      const int kt = f >> 5, gg = (f >> 3) & 3, o = f & 7;
+      uint16_t v3[8];
 #pragma unroll
-    for (int q = 0; q < P2; ++q) {
-      const int e = tid + q * 64 * VT_WAVES;
-      v2[q] = *reinterpret_cast<const u32x4*>(W2 + (e >> 5) * HID + 8 * (e & 31));
-    }
-#pragma unroll
-    for (int q = 0; q < P1; ++q) {
-      const int e = tid + q * 64 * VT_WAVES, f = e >> 6, l = e & 63;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int k = kslot(l >> 4, j);
-        v1[q][j] = k < 23 ? W1[(16 * f + (l & 15)) * 23 + k] : (uint16_t)0;
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < P2; ++q) {
-      const int e = tid + q * 64 * VT_WAVES, rw = e >> 5, c = 8 * (e & 31);
-      const int o = c & 31, g0 = (o & 15) >> 2, rr = rw & 15;
-      char* frag = reinterpret_cast<char*>(&S.w2[rw >> 4][c >> 5][0]) + 8 * (o >> 4);
-      *reinterpret_cast<uint2*>(frag + 16 * slot(16 * g0 + rr)) = uint2{v2[q].x, v2[q].y};
-      *reinterpret_cast<uint2*>(frag + 16 * slot(16 * (g0 + 1) + rr)) = uint2{v2[q].z, v2[q].w};
-    }
-#pragma unroll
-    for (int q = 0; q < P1; ++q) {
-      const int e = tid + q * 64 * VT_WAVES, f = e >> 6, l = e & 63;
+      for (int j = 0; j < 8; ++j) v3[j] = W3[frag ? o * HID + 32 * kt + kslot(gg, j) : j * HID + f];
+      const float ls = log_std[tid & 7], vb3 = b[2 * HID + (tid & 7)];
+      st.store(S.w1, S.w2, wave, lane, slot);
       bf16x8 v;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = bf16_of_bits(v1[q][j]);
-      S.w1[f][l] = v;
-    }
-    for (int i = tid; i < HID; i += 64 * VT_WAVES) {
-      if constexpr (!POL) S.w3[i] = (float)bf16_of_bits(W3[i]);
-      S.b1k[i] = b[i] * TWO_LOG2E;
-      S.b2k[i] = b[HID + i] * TWO_LOG2E;
-    }
-    if constexpr (POL) {
-      // W3[o][f] at W3[o * HID + f]: output-layer fragments, one per thread (K tile tid / 32,
-      // lane row (tid / 8) % 4, output tid % 8), and the transposed copy
-      if (tid < 8 * 32) {
-        const int kt = tid >> 5, gg = (tid >> 3) & 3, o = tid & 7;
-        bf16x8 v;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = bf16_of_bits(W3[o * HID + 32 * kt + kslot(gg, j)]);
-        S.w3a[kt][8 * gg + o] = v;
-      }
-      for (int e = tid; e < 8 * HID; e += 64 * VT_WAVES) S.w3t[e >> 3][e & 7] = W3[(e & 7) * HID + (e >> 3)];
+      for (int j = 0; j < 8; ++j) v[j] = bf16_of_bits(v3[j]);
+      *(frag ? &S.w3a[kt][8 * gg + o] : reinterpret_cast<bf16x8*>(&S.w3t[f][0])) = v;
       if (tid < 8) {
-        const float ls = log_std[tid];
-        S.b3[tid] = b[2 * HID + tid];
+        S.b3[tid] = vb3;
         S.ls[tid] = ls;
         S.ivar[tid] = expf(-2.0f * ls);
       }
+    } else {
+      const uint16_t v3 = W3[f];
+      st.store(S.w1, S.w2, wave, lane, slot);
+      if (tid < HID) S.w3[f] = (float)bf16_of_bits(v3);
+    }
+    if (tid < HID) {
+      S.b1k[f] = vb1 * TWO_LOG2E;
+      S.b2k[f] = vb2 * TWO_LOG2E;
     }
   }
   const f32x4 zero = f32x4{0, 0, 0, 0};
@@ -592,7 +561,6 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
   float mean = 0.0f, inv_std = 1.0f;
   if (POL && hp.normalize) adv_stats(W.adv_part, B, lane, mean, inv_std);   // every wave, the same bits
   __syncthreads();
-  const float b3 = POL ? 0.0f : b[2 * HID];
 
   for (; t < tiles; t += stride) {
     // the lane as this tile sees it: the weights in LDS, which no iteration changes, would
