@@ -50,10 +50,10 @@ int launch_mlp_forward(const auv_mlp* net, int n, const float* obs, float* out, 
 int launch_stats_reduce(const float* work, int T, int G, float* stats, hipStream_t s);
 
 // Per-workgroup partial sums of an MLP's parameter gradient (layouts of the PPO update):
-// part_w1 [G][256][32], part_b1 [G][256], part_w2 [G][256][256], part_w3t [G][256][16]
-// (dW3 transposed), part_b2 [G][256], part_b3 [G][16], part_ls [G][16] (d log_std).
+// part_w1 [G][256][32], part_b1 [G][256], part_w2 [G][256][256], part_w3 [G][n_out][256],
+// part_b2 [G][256], part_b3 [G][16], part_ls [G][16] (d log_std).
 struct GradParts {
-  float *part_w1, *part_b1, *part_w2, *part_w3t, *part_b2, *part_b3, *part_ls;
+  float *part_w1, *part_b1, *part_w2, *part_w3, *part_b2, *part_b3, *part_ls;
 };
 // launches implemented in ppo.hip: dW2 = q(dz2) q(h1)^T over `steps` 32-sample steps of
 // half-fragment arrays (steps a multiple of 4), one partial per group; the fixed-order sum of

@@ -66,7 +66,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));   // four bf16: a ha
 struct Work {
   double* adv_part;     // [ADV_BLOCKS][2] sums of A and A^2
   u32x2* dz2_half;      // [Bp/16][16 feature tiles][64 lanes] q(dz2) half fragments
-  float* part_w3t;      // [G][256 f][16 j] dW3^T
+  float* part_w3;       // [G][n_out][256] dW3
   float* part_b2;       // [G][256]
   float* part_b3;       // [G][16]
   float* part_ls;       // [G][16]
@@ -103,7 +103,7 @@ inline size_t work_layout(int B, size_t off[WORK_PARTS]) {
   const size_t Bp = (size_t)padded(B), G = MAX_GROUPS;
   const bool recomp = (int)(Bp / 32) >= VW_RECOMP_STEPS;
   const size_t sizes[WORK_PARTS] = {2 * sizeof(double) * ADV_BLOCKS, Bp * HID * 2,
-                            G * HID * 16 * 4, G * HID * 4, G * 16 * 4, G * 16 * 4, 2 * G * STATS * 4,
+                            G * 8 * HID * 4, G * HID * 4, G * 16 * 4, G * 16 * 4, 2 * G * STATS * 4,
                             G * HID * 32 * 4, G * HID * 4, G * HID * HID * 4,
                             2 * (size_t)red_blocks(8) * 4,
                             Bp / 16 * 64 * 16, Bp * HID * 2, recomp ? 0 : Bp * HID * 2};
@@ -122,7 +122,7 @@ inline Work work_at(void* base, int B) {
   Work W;
   W.adv_part = (double*)(p + off[0]);
   W.dz2_half = (u32x2*)(p + off[1]);
-  W.part_w3t = (float*)(p + off[2]);
+  W.part_w3 = (float*)(p + off[2]);
   W.part_b2 = (float*)(p + off[3]);
   W.part_b3 = (float*)(p + off[4]);
   W.part_ls = (float*)(p + off[5]);
@@ -829,11 +829,11 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
       W.part_b2[(size_t)wg * HID + tid] = v;
     }
     for (int o = tid; o < 8 * HID; o += 64 * VT_WAVES) {
-      const int f = o >> 3, j = o & 7;
+      const int j = o / HID, f = o - j * HID;
       float v = 0.0f;
 #pragma unroll
       for (int wv = 0; wv < VT_WAVES; ++wv) v += U.red.w3[wv][f][j];
-      W.part_w3t[((size_t)wg * HID + f) * 16 + j] = v;
+      W.part_w3[(size_t)wg * 8 * HID + o] = v;
     }
     if (tid < 16) {
       const int q = tid >> 3, o = tid & 7;
@@ -869,7 +869,7 @@ __global__ __launch_bounds__(64 * VT_WAVES, 1) void k_vtile(const uint16_t* __re
       else if (q == 0)
         W.part_b2[(size_t)wg * HID + f] = v;
       else
-        W.part_w3t[((size_t)wg * HID + f) * 16] = v;
+        W.part_w3[(size_t)wg * HID + f] = v;
     }
     if (tid < 2) {
       float v = 0.0f;
@@ -1405,7 +1405,9 @@ __device__ __forceinline__ void adam_entry(const AdamFuse& A, int e, float g0, f
 }
 
 // Packed gradient of one network = fixed-order sums of the partials, and per-block sums of
-// squares for the global norm.  A block owns 64 gradient entries (one per lane); its four
+// squares for the global norm.  Every partial lies in the order of the gradient's entries, so that a
+// wave's loads are contiguous (dW3 transposed, 64 bytes between lanes, cost 6 us of the 13 at 256
+// groups).  A block owns 64 gradient entries (one per lane); its four
 // waves each sum a contiguous quarter of the workgroup partials with eight loads in flight,
 // then wave 0 adds the quarters in wave order.  G1: forward/backward groups (dW3, db2, db3,
 // d log_std), G2: dW1 groups, Gb1: db1 groups, G3: dW2 groups.
@@ -1428,8 +1430,7 @@ __global__ __launch_bounds__(256) void k_reduce(int n_out, int n_act, int G1, in
     } else if ((q -= nW1) < nW2) {
       src = W.part_w2 + q, stride = (size_t)HID * HID, G = G3;
     } else if ((q -= nW2) < nW3) {
-      const int j = q / HID, f = q - HID * j;
-      src = W.part_w3t + f * 16 + j, stride = (size_t)HID * 16, G = G1;
+      src = W.part_w3 + q, stride = (size_t)nW3, G = G1;
     } else if ((q -= nW3) < HID) {
       src = W.part_b1 + q, stride = HID, G = Gb1;
     } else if ((q -= HID) < HID) {
@@ -1570,7 +1571,7 @@ int launch_grad_reduce(const GradParts& P, int n_out, int n_act, int G1, int G2,
   W.part_w1 = P.part_w1;
   W.part_b1 = P.part_b1;
   W.part_w2 = P.part_w2;
-  W.part_w3t = P.part_w3t;
+  W.part_w3 = P.part_w3;
   W.part_b2 = P.part_b2;
   W.part_b3 = P.part_b3;
   W.part_ls = P.part_ls;

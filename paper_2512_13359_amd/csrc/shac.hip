@@ -811,18 +811,19 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
   if (MODE == MODE_EXTERNAL || !A.want_grad) return;
   const size_t wg = blockIdx.x;
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int m = 0; m < 4; ++m) {
+    if (r < ACT) *reinterpret_cast<f32x4*>(&P_.part_w3[(wg * ACT + r) * HID + 64 * w + 16 * m + 4 * g]) = sums.w3[m];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const size_t f = wg * HID + 64 * w + 16 * m + 4 * g + q;
       P_.part_w1[f * 32 + r] = r < ONES ? sums.w1[m][q] : 0.0f;
       P_.part_w1[f * 32 + 16 + r] = 0.0f;   // inputs 12.. of the paper task are zero
-      P_.part_w3t[f * 16 + r] = sums.w3[m][q];
       if (r == ONES) {
         P_.part_b1[f] = sums.w1[m][q];
         P_.part_b2[f] = sums.z2[m][q];
       }
     }
+  }
   if (w == 0) {
     float b3 = sums.b3;   // over the lane rows g, in a fixed order
     b3 += __shfl_xor(b3, 16);
@@ -920,7 +921,7 @@ inline size_t work_layout(int N, int h, size_t off[WORK_PARTS]) {
       Np * 4, Np * 4, Np * 4,               // 3 J, 4 Jr, 5 V(o_h)
       half * 16, half * 16,                 // 6 h1, 7 dz2
       G * HID * 32 * 4, G * HID * 4,        // 8 part_w1, 9 part_b1
-      G * HID * 16 * 4, G * HID * 4,        // 10 part_w3t, 11 part_b2
+      G * ACT * HID * 4, G * HID * 4,       // 10 part_w3, 11 part_b2
       G * 16 * 4 + G * 16 * 4,              // 12 part_b3 + part_ls
       G * HID * HID * 4,                    // 13 part_w2
       4096 * 4,                             // 14 per-block sums of squares
@@ -1040,7 +1041,7 @@ int auv_shac_window(auv_env* env, const auv_shac_config* cfg, const auv_mlp* pol
   GradParts P;
   P.part_w1 = (float*)at(8);
   P.part_b1 = (float*)at(9);
-  P.part_w3t = (float*)at(10);
+  P.part_w3 = (float*)at(10);
   P.part_b2 = (float*)at(11);
   P.part_b3 = (float*)at(12);
   P.part_ls = P.part_b3 + MAX_GROUPS * 16;
