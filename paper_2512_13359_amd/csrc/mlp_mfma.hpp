@@ -60,13 +60,17 @@ __device__ __forceinline__ bf16x8 act_frag(const f32x4& d0, const f32x4& d1, con
 // piece of row 16 mt + r at columns 32 kt + o .. + 7 (o = 0, 8, 16, 24) is the half o / 16 (K slots
 // 4 (o / 16) .. + 3) of lanes 16 g + r and 16 (g + 1) + r, g = (o % 16) / 4.  A wave's load takes 128
 // bytes of each of eight rows: its stores then meet on a bank at most four at a time (with two whole
-// rows per load sixteen at a time, 3 us of every launch that stages the weights).
+// rows per load sixteen at a time, 3 us of every launch that stages the weights).  W1's rows have 23
+// inputs: lane (g, r) reads inputs 4 g .. + 3 and 16 + 4 g .. + 3 of its row as 8 bytes each, not
+// aligned, those past the row masked (the last row's reach into W2, which follows).  A load in
+// which every lane reads another row goes through the L1 at one lane per cycle, so their number is
+// what counts: two per fragment, not eight.
 template <int WAVES>
 struct StageWeights {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   static constexpr int P2 = HID * HID / 8 / (64 * WAVES), P1 = 16 / WAVES;
   u32x4 v2[P2];
-  uint16_t v1[P1][8];
+  uint2 v1[P1][2];
 
   __device__ __forceinline__ static int row(int q, int wave, int lane) { return 8 * ((q * WAVES + wave) >> 2) + (lane >> 3); }
   __device__ __forceinline__ static int col(int q, int wave, int lane) {
@@ -80,8 +84,8 @@ struct StageWeights {
 #pragma unroll
     for (int q = 0; q < P1; ++q)
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
-        v1[q][j] = w1[(16 * (q * WAVES + wave) + (lane & 15)) * 23 + min(kslot(lane >> 4, j), 22)];
+      for (int h = 0; h < 2; ++h)
+        __builtin_memcpy(&v1[q][h], w1 + (16 * (q * WAVES + wave) + (lane & 15)) * 23 + min(kslot(lane >> 4, 4 * h), 20), 8);
   }
   template <class Slot>
   __device__ __forceinline__ void store(bf16x8 (*w1)[64], bf16x8 (*w2)[8][64], int wave, int lane, Slot slot) const {
@@ -94,9 +98,11 @@ struct StageWeights {
     }
 #pragma unroll
     for (int q = 0; q < P1; ++q) {
+      const uint32_t d[4] = {v1[q][0].x, v1[q][0].y, v1[q][1].x, v1[q][1].y};
       bf16x8 v;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) v[j] = bf16_of_bits(kslot(lane >> 4, j) < 23 ? v1[q][j] : (uint16_t)0);
+      for (int j = 0; j < 8; ++j)
+        v[j] = bf16_of_bits(kslot(lane >> 4, j) < 23 ? (uint16_t)(d[j >> 1] >> (16 * (j & 1))) : (uint16_t)0);
       w1[q * WAVES + wave][lane] = v;
     }
   }

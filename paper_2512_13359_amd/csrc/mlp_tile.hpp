@@ -25,38 +25,37 @@ struct TileMlpRegs {
   f32x4 b2[MT];       // layer-2 bias x 2 log2 e of this lane's accumulator rows [M-tile]
 };
 
-// Weights of MLP wave m into registers (policy layout of auv_mlp: W1 [256][23], W2
-// [256][256], W3 [n_out][256] as bf16 bits, biases b1, b2, b3 as fp32).
+// Layer-3 weights and layer-2 biases of MLP wave m into registers (policy layout of auv_mlp: W1
+// [256][23], W2 [256][256], W3 [n_out][256] as bf16 bits, biases b1, b2, b3 as fp32).
 template <int FPW>
 __device__ __forceinline__ void tile_mlp_load(const uint16_t* __restrict__ w, const float* __restrict__ b, int n_out,
                                               int m, int lane, TileMlpRegs<FPW>& R) {
   constexpr int MT = FPW / 16, KO = FPW / 32;
   const int g = lane >> 4, r = lane & 15;
-  const uint16_t* W1 = w;
-  const uint16_t* W2 = w + HID * 23;
-  const uint16_t* W3 = W2 + HID * HID;
+  const uint16_t* W3 = w + HID * 23 + HID * HID;
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    const int row = FPW * m + 16 * mt + r;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int k = kslot(g, j);
-      R.w1[mt][j] = k < 23 ? bf16_of_bits(W1[row * 23 + k]) : bf16_of_bits(0);
-    }
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      const int kt = (KO * m + kk) & 7;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) R.w2[mt][kk][j] = bf16_of_bits(W2[row * HID + 32 * kt + kslot(g, j)]);
-    }
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int ii = 0; ii < 4; ++ii) R.b2[mt][ii] = b[HID + FPW * m + 16 * mt + 4 * g + ii] * TWO_LOG2E;
-  }
 #pragma unroll
   for (int i = 0; i < KO; ++i)
 #pragma unroll
     for (int j = 0; j < 8; ++j)
       R.w3[i][j] = r < n_out ? bf16_of_bits(W3[r * HID + 32 * (KO * m + i) + kslot(g, j)]) : bf16_of_bits(0);
+}
+
+// Its fragments of W1 and W2 from the staged copy (lane (g, r) of fragment (M-tile, K tile): row
+// 16 mt + r, inputs 32 kt + kslot(g, j)).
+template <int FPW>
+__device__ __forceinline__ void tile_mlp_fragments(const bf16x8 (*w1)[64], const bf16x8 (*w2)[8][64], int m, int lane,
+                                                   TileMlpRegs<FPW>& R) {
+  constexpr int MT = FPW / 16, KO = FPW / 32;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    R.w1[mt] = w1[MT * m + mt][lane];
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) R.w2[mt][kk] = w2[MT * m + mt][(KO * m + kk) & 7][lane];
+  }
 }
 
 // Layer 1 of one tile (x = its layer-1 operand fragment): this wave's K tiles of the

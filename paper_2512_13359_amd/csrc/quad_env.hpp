@@ -329,12 +329,13 @@ __device__ __forceinline__ void wrench(const float Tf[8], const float Tm[8], flo
 // ------------------------------------------------------ allocation table in LDS ----
 // Rows c = 0..2: force row c, rows 4 + c: moment row c, each x f_max; rows 3 and 7 zero
 // (lane 3 of a quad reads them).  Written by the first 64 threads of the block.
+__device__ __forceinline__ float alloc_entry(const VehArgs& V, int tid) {   // entry tid of the table
+  const int row = (tid >> 3) & 7, j = tid & 7;
+  const int src = row < 3 ? row : (row >= 4 && row < 7 ? row - 1 : -1);
+  return src >= 0 ? V.alloc[src * 8 + j] * V.f_max : 0.0f;
+}
 __device__ __forceinline__ void stage_alloc(const VehArgs& V, float (*alloc)[8], int tid) {
-  if (tid < 64) {
-    const int row = tid >> 3, j = tid & 7;
-    const int src = row < 3 ? row : (row >= 4 && row < 7 ? row - 1 : -1);
-    alloc[row][j] = src >= 0 ? V.alloc[src * 8 + j] * V.f_max : 0.0f;
-  }
+  if (tid < 64) alloc[tid >> 3][tid & 7] = alloc_entry(V, tid);
 }
 
 __device__ __forceinline__ void alloc_rows(const float (*alloc)[8], int c, float Tf[8], float Tm[8]) {
@@ -362,11 +363,9 @@ struct QEnv {
 // rotation vector, 6-8 v, 9-11 omega, 12-14 / 15-17 the moving averages of the force /
 // torque commands (state, kept in u0 / u1 of lanes 0-2).
 template <bool PAPER = false>
-__device__ __forceinline__ void load_env(const VehArgs& V, const EnvArgs& E, const QK& K, int i, bool valid,
-                                         QEnv& X, QModel& M, QRef& F) {
-  const int c = K.c, cv = c < 3 ? c : 0;   // cv: a valid row for lane 3's loads
+__device__ __forceinline__ void load_buffers(const EnvArgs& E, int c, int i, bool valid, QEnv& X, Params& P) {
+  const int cv = c < 3 ? c : 0;   // a valid row for lane 3's loads
   const size_t N = (size_t)E.n;
-  Params P;
   if (valid) {
     X.p = c < 3 ? E.state[cv * N + i] : 0.0f;
     X.q = E.state[(c < 3 ? 4 + c : 3) * N + i];
@@ -394,6 +393,14 @@ __device__ __forceinline__ void load_env(const VehArgs& V, const EnvArgs& E, con
     P = Params{{1, 1, 1}, {0, 0, 0}, {0, 0, 0}, {1, 0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, 0, 0};
     X.ob = QObs{0, 0, 0};
   }
+}
+
+// The same with the lane's model and reference constants.
+template <bool PAPER = false>
+__device__ __forceinline__ void load_env(const VehArgs& V, const EnvArgs& E, const QK& K, int i, bool valid,
+                                         QEnv& X, QModel& M, QRef& F) {
+  Params P;
+  load_buffers<PAPER>(E, K.c, i, valid, X, P);
   make_lane_consts<PAPER>(V, K, P, M, F);
 }
 
