@@ -473,7 +473,8 @@ __device__ __forceinline__ void report_status(uint32_t* status, uint32_t nonfini
 // Sum over the 64 lanes of a wave in a fixed butterfly order (every lane gets the sum).
 // DPP lane moves for reductions (GCN row = 16 lanes): rotate right within each row, and
 // broadcast lane 15 / 31 into the following row(s) (rows outside row_mask read zero).
-constexpr int DPP_ROW_ROR4 = 0x124, DPP_ROW_ROR8 = 0x128, DPP_ROW_BCAST15 = 0x142, DPP_ROW_BCAST31 = 0x143;
+constexpr int DPP_ROW_ROR4 = 0x124, DPP_ROW_ROR8 = 0x128, DPP_ROW_ROR12 = 0x12C, DPP_ROW_BCAST15 = 0x142,
+              DPP_ROW_BCAST31 = 0x143;
 constexpr int DPP_QUAD_SWAP1 = 0xB1, DPP_QUAD_SWAP2 = 0x4E;   // quad_perm [1,0,3,2], [2,3,0,1]
 
 template <int CTRL, int ROW_MASK = 0xF>
@@ -504,6 +505,22 @@ __device__ __forceinline__ float wave_sum_quads(float v) {
   v += dpp_move<DPP_ROW_ROR4>(v);
   v += dpp_move<DPP_ROW_ROR8>(v);
   return rows_sum(v);
+}
+
+// The same sums, added in the same order ((q3 + q2) + (q1 + q0) in a row, the rows alike), of four
+// values at once: lane c of every quad holds its quad's term of value c on entry and value c's sum
+// at the end.
+__device__ __forceinline__ float lanes_sum_quads(float v, int lane) {
+  const float up = dpp_move<DPP_ROW_ROR12>(v), down = dpp_move<DPP_ROW_ROR4>(v);
+  v += (lane & 4) ? down : up;                // quad ^ 1
+  v += dpp_move<DPP_ROW_ROR8>(v);             // quad ^ 2
+  v += __shfl_xor(v, 16);
+  v += __shfl_xor(v, 32);
+  return v;
+}
+
+__device__ __forceinline__ uint32_t quad_swap1(uint32_t x) {   // the value of lane l ^ 1
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, DPP_QUAD_SWAP1, 0xF, 0xF, true);
 }
 
 }  // namespace auv

@@ -133,6 +133,12 @@ __global__ __launch_bounds__(64) void k_env_loop(VehArgs V, EnvArgs E, int T, ui
 // faster loop while the batch leaves SIMDs idle.  PAPER: the paper's own task (6-D wrench
 // action, lane c < 3 holding action components c and 3 + c; 12-D observation; five-term
 // reward with the action moving average; gravity factor), which only this loop runs.
+//
+// With one wave per SIMD the time of a step is the instructions it issues, so what is the same in
+// the four lanes of a quad is dealt over them: lane c finishes the reward (two square roots, an
+// arc tangent), the outputs and the statistics of step t with t % 4 = c, all four lanes at every
+// fourth step, and each pair of lanes draws its action block for two steps, one lane for each.
+// 4001 environments x 200 random steps: 279 -> 230 us.  Same bits.
 template <bool EXTERNAL, bool PAPER>
 __global__ __launch_bounds__(64) void k_env_quad(VehArgs V, EnvArgs E, int T, uint32_t gstep0, StepOut O) {
   __shared__ float alloc[8][8];
@@ -157,6 +163,10 @@ __global__ __launch_bounds__(64) void k_env_quad(VehArgs V, EnvArgs E, int T, ui
   quad::load_env<PAPER>(V, E, K, i, valid, X, M, F);
   if (O.traj && valid) quad::store_state(O.traj, (size_t)(T + 1) * N, (size_t)i, c, X);
   StatsBuf SB{};
+  // this lane's step of the last four: |dp|^2, the attitude error's parts, the action's squared norm
+  // (PAPER: |dp| and the reward in the first and the last), and whether an episode ended
+  float pk_d = 0.0f, pk_v = 0.0f, pk_w = 0.0f, pk_u = 0.0f, pk_done = 0.0f;
+  float na0 = 0.0f, na1 = 0.0f;   // random actions of the odd step of a pair
   uint32_t nf = 0;   // non-finite state components (this lane's share) at episode ends
   for (int t = 0; t < T; ++t) {
     const size_t ti = (size_t)t * N + (size_t)i;
@@ -165,10 +175,19 @@ __global__ __launch_bounds__(64) void k_env_quad(VehArgs V, EnvArgs E, int T, ui
     if (EXTERNAL) {
       a0 = (valid && acts) ? O.act[ra0 * TN + ti] : 0.0f;
       a1 = (valid && acts) ? O.act[ra1 * TN + ti] : 0.0f;
-    } else {        // words (x, y) or (z, w) of Philox block c / 2 of this step
-      const U4 r = philox(U4{gid, gstep0 + (uint32_t)t, 1u, (uint32_t)(c >> 1)}, E.key0, E.key1);
-      a0 = acts ? 2.0f * u01((c & 1) ? r.z : r.x) - 1.0f : 0.0f;
-      a1 = acts ? 2.0f * u01((c & 1) ? r.w : r.y) - 1.0f : 0.0f;
+    } else {        // words (x, y) (even c) or (z, w) of Philox block c / 2 of this step
+      if ((t & 1) == 0) {   // even lanes draw the block of step t, odd lanes that of t + 1
+        const bool odd = c & 1;
+        const U4 r = philox(U4{gid, gstep0 + (uint32_t)t + (odd ? 1u : 0u), 1u, (uint32_t)(c >> 1)}, E.key0, E.key1);
+        const uint32_t g0 = quad_swap1(odd ? r.x : r.z), g1 = quad_swap1(odd ? r.y : r.w);
+        a0 = acts ? 2.0f * u01(odd ? g0 : r.x) - 1.0f : 0.0f;
+        a1 = acts ? 2.0f * u01(odd ? g1 : r.y) - 1.0f : 0.0f;
+        na0 = acts ? 2.0f * u01(odd ? r.z : g0) - 1.0f : 0.0f;
+        na1 = acts ? 2.0f * u01(odd ? r.w : g1) - 1.0f : 0.0f;
+      } else {
+        a0 = na0;
+        a1 = na1;
+      }
       if (O.act && valid && acts) {
         O.act[ra0 * TN + ti] = a0;
         O.act[ra1 * TN + ti] = a1;
@@ -186,36 +205,52 @@ __global__ __launch_bounds__(64) void k_env_quad(VehArgs V, EnvArgs E, int T, ui
     const float tfi = tf * M.iMlin;
     for (int s = 0; s < E.substeps; ++s) quad::rk4(K, M, tfi, tm, E.h, X.p, X.q, X.v, X.om);
     X.ep += 1;
-    float pr, qr, dist, reward;
+    float pr, qr;
     quad::reference(E, K, F, X.ep, pr, qr);
     quad::QRefCols rc;
+    const bool mine = c == (t & 3);
     if (PAPER) {
+      float dist;
       quad::observe_paper(K, X.p, X.q, pr, qr, X.ob, dist);
-      reward = quad::paper_reward(E.tk, dc, X.ob, X.om, uf, ut, X.u0, X.u1);
+      const float reward = quad::paper_reward(E.tk, dc, X.ob, X.om, uf, ut, X.u0, X.u1);
       X.u0 = __builtin_fmaf(E.tk.beta, X.u0, (1.0f - E.tk.beta) * uf);
       X.u1 = __builtin_fmaf(E.tk.beta, X.u1, (1.0f - E.tk.beta) * ut);
+      pk_d = mine ? dist : pk_d;
+      pk_u = mine ? reward : pk_u;
     } else {
+      float d_sq, vec_sq, ew;
       rc = quad::ref_columns(K, qr);
-      quad::observe(K, X.p, X.q, pr, rc, X.ob, dist);
-      const float theta = quad::attitude_error(K, X.q, qr);
-      reward = -dist - 0.5f * theta - 0.01f * usq;
+      quad::observe_sq(K, X.p, X.q, pr, rc, X.ob, d_sq);
+      quad::attitude_parts(K, X.q, qr, vec_sq, ew);
+      pk_d = mine ? d_sq : pk_d;
+      pk_v = mine ? vec_sq : pk_v;
+      pk_w = mine ? ew : pk_w;
+      pk_u = mine ? usq : pk_u;
     }
-    const bool done = (X.ep == E.H);
-    if (done) {   // the whole quad
+    if (X.ep == E.H) {   // the whole quad
       float dist0;
+      pk_done = mine ? 1.0f : pk_done;
       nf += quad::nonfinite_quad(c, X);
       quad::new_episode<PAPER>(V, E, K, gid, i, valid, X, M, F, pr, qr, rc, dist0);
     }
-    if (O.stats_work) {   // reward, done and dist are the same in the four lanes of a quad
-      const float sr = wave_sum_quads(valid ? reward : 0.0f);
-      const float sd = wave_sum_quads((valid && done) ? 1.0f : 0.0f);
-      const float sp = wave_sum_quads(valid ? dist : 0.0f);
-      stats_park(SB, O.stats_work, T, t, lane, blockIdx.x, gridDim.x, sr, sd, sp);
-    }
-    if (valid && c == 0) {
-      if (O.reward) O.reward[ti] = reward;
-      if (O.done) O.done[ti] = done ? 1.0f : 0.0f;
-      if (O.done_u8) O.done_u8[i] = done ? 1 : 0;
+    if ((t & 3) == 3 || t == T - 1) {   // rewards, outputs and sums of steps t - t % 4 .. t, lane c that of step tl
+      const int tl = (t & ~3) + c;
+      const float dist = PAPER ? pk_d : sqrtf(pk_d);
+      const float reward = PAPER ? pk_u : -dist - 0.5f * quad::attitude_angle(pk_v, pk_w) - 0.01f * pk_u;
+      if (O.stats_work) {
+        const float sr = lanes_sum_quads(valid ? reward : 0.0f, lane);
+        const uint64_t ended = __ballot(valid && pk_done != 0.0f) & (0x1111111111111111ull << c);
+        const float sd = (float)__popcll(ended);
+        const float sp = lanes_sum_quads(valid ? dist : 0.0f, lane);
+        stats_park4(SB, O.stats_work, T, t, lane, blockIdx.x, gridDim.x, sr, sd, sp);
+      }
+      if (valid && tl <= t) {
+        const size_t ti = (size_t)tl * N + (size_t)i;
+        if (O.reward) O.reward[ti] = reward;
+        if (O.done) O.done[ti] = pk_done;
+        if (O.done_u8 && tl == t) O.done_u8[i] = pk_done != 0.0f ? 1 : 0;
+      }
+      pk_done = 0.0f;
     }
     if (O.traj && valid) quad::store_state(O.traj, (size_t)(T + 1) * N, (size_t)(t + 1) * N + i, c, X);
   }

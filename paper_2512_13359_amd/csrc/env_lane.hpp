@@ -90,10 +90,9 @@ __device__ __forceinline__ void lane_step(const VehArgs& V, const EnvArgs& E, ui
 // ([3][G][T] layout), so each step costs no memory traffic of its own.
 struct StatsBuf { float v[3]; };
 
-__device__ __forceinline__ void stats_park(StatsBuf& B, float* __restrict__ work, int T, int t, int lane,
-                                           int g, int G, float sr, float sd, float sp) {
+__device__ __forceinline__ void stats_flush(const StatsBuf& B, float* __restrict__ work, int T, int t, int lane,
+                                            int g, int G) {
   const int slot = t & 63;
-  if (lane == slot) { B.v[0] = sr; B.v[1] = sd; B.v[2] = sp; }
   if (slot == 63 || t == T - 1) {
     const int t0 = t - slot;
     if (lane <= slot) {
@@ -101,6 +100,19 @@ __device__ __forceinline__ void stats_park(StatsBuf& B, float* __restrict__ work
       for (int s = 0; s < 3; ++s) work[((size_t)s * G + g) * T + t0 + lane] = B.v[s];
     }
   }
+}
+
+__device__ __forceinline__ void stats_park(StatsBuf& B, float* __restrict__ work, int T, int t, int lane,
+                                           int g, int G, float sr, float sd, float sp) {
+  if (lane == (t & 63)) { B.v[0] = sr; B.v[1] = sd; B.v[2] = sp; }
+  stats_flush(B, work, T, t, lane, g, G);
+}
+
+// Steps t - t % 4 .. t at once, lane l holding the sums of step t - t % 4 + l % 4.
+__device__ __forceinline__ void stats_park4(StatsBuf& B, float* __restrict__ work, int T, int t, int lane,
+                                            int g, int G, float sr, float sd, float sp) {
+  if ((lane & ~3) == (t & 60)) { B.v[0] = sr; B.v[1] = sd; B.v[2] = sp; }
+  stats_flush(B, work, T, t, lane, g, G);
 }
 
 __device__ __forceinline__ void stats_push(StatsBuf& B, float* __restrict__ work, int T, int t, int lane,

@@ -256,25 +256,36 @@ __device__ __forceinline__ QRefCols ref_columns(const QK& K, float qr) {
 }
 
 // Observation components of this lane (body-frame position error and the body-frame
-// reference columns) and |dp|.
+// reference columns) and |dp| or its square.
 struct QObs { float dpb, c0, c1; };
-__device__ __forceinline__ void observe(const QK& K, float p, float q, float pr, const QRefCols& rc, QObs& o,
-                                        float& dist) {
+__device__ __forceinline__ void observe_sq(const QK& K, float p, float q, float pr, const QRefCols& rc, QObs& o,
+                                           float& dist_sq) {
   const QRot R = qrot(K, q);
   o.dpb = rot_T(R, pr - p);
   o.c0 = rot_T(R, rc.r0);
   o.c1 = rot_T(R, rc.r1);
-  dist = sqrtf(qsum(o.dpb * o.dpb));
+  dist_sq = qsum(o.dpb * o.dpb);
+}
+__device__ __forceinline__ void observe(const QK& K, float p, float q, float pr, const QRefCols& rc, QObs& o,
+                                        float& dist) {
+  observe_sq(K, p, q, pr, rc, o, dist);
+  dist = sqrtf(dist);
 }
 
 // Attitude-error angle 2 atan2(|vec(q_err)|, |scalar(q_err)|) of q_err = q^* (x) q_ref:
-// scalar w wr + e.er, vector w er - wr e - e x er.
-__device__ __forceinline__ float attitude_error(const QK& K, float q, float qr) {
+// scalar w wr + e.er, vector w er - wr e - e x er; from the vector's squared norm and the scalar.
+__device__ __forceinline__ void attitude_parts(const QK& K, float q, float qr, float& vec_sq, float& ew) {
   const float e = q * K.m3, er = qr * K.m3;
   const float wb = dpp<BC3>(q), wr = dpp<BC3>(qr);
-  const float ew = qsum(q * qr);
+  ew = qsum(q * qr);
   const float vec = __builtin_fmaf(wb, er, -wr * e) - cross(e, perm(er));
-  return 2.0f * atan2f(sqrtf(qsum(vec * vec)), fabsf(ew));
+  vec_sq = qsum(vec * vec);
+}
+__device__ __forceinline__ float attitude_angle(float vec_sq, float ew) { return 2.0f * atan2f(sqrtf(vec_sq), fabsf(ew)); }
+__device__ __forceinline__ float attitude_error(const QK& K, float q, float qr) {
+  float vec_sq, ew;
+  attitude_parts(K, q, qr, vec_sq, ew);
+  return attitude_angle(vec_sq, ew);
 }
 
 // Observation of the paper task: body-frame position error and the rotation vector of

@@ -193,6 +193,32 @@ def test_step_api_matches_rollout_and_is_deterministic():
     assert np.array_equal(host(a.params), host(b.params))
 
 
+@pytest.mark.parametrize("paper", [False, True])
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 5, 63, 64, 65, 67, 130])
+def test_quad_loop_step_groups(T, paper):
+    """The quad loop finishes rewards, done flags and sums for up to four steps at once and draws actions for two:
+    every remainder of T, with episodes ending at any place in a group (length 7), gives what single steps give."""
+    require_gpu()
+    announce(f"quad loop in groups of steps T={T} paper={paper}")
+    cfg = W.config("c2", n_envs=37, episode_len=7)
+    if paper:
+        cfg["flags"] = 0
+    a, b = gpu_env(cfg), gpu_env(cfg)
+    for e in (a, b):
+        if paper:
+            e.set_task(W.PAPER_TASK)
+        e.reset()
+    bufs = a.rollout_buffers(T, record=("reward", "done", "stats"))
+    a.rollout(T, W.MODE_RANDOM, bufs=bufs)
+    for t in range(T):
+        r, d, s = b.step(W.MODE_RANDOM, want_stats=True)
+        assert torch.equal(r, bufs["reward"][t]), t
+        assert torch.equal(d.float(), bufs["done"][t]), t
+        assert d.float().sum() == s[1], t
+        assert torch.equal(s, bufs["stats"][:, t]), t
+    assert torch.equal(a.state, b.state) and torch.equal(a.obs, b.obs)
+
+
 def test_checkpoint_resume_bit_exact():
     """T steps in one go equal T/2 steps, a copy of the state buffers and step counter
     into a fresh handle, and T/2 more steps."""
