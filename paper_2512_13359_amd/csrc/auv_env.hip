@@ -166,7 +166,7 @@ __global__ __launch_bounds__(64) void k_env_quad(VehArgs V, EnvArgs E, int T, ui
   // this lane's step of the last four: |dp|^2, the attitude error's parts, the action's squared norm
   // (PAPER: |dp| and the reward in the first and the last), and whether an episode ended
   float pk_d = 0.0f, pk_v = 0.0f, pk_w = 0.0f, pk_u = 0.0f, pk_done = 0.0f;
-  float na0 = 0.0f, na1 = 0.0f;   // random actions of the odd step of a pair
+  quad::StepWords RW{};
   uint32_t nf = 0;   // non-finite state components (this lane's share) at episode ends
   for (int t = 0; t < T; ++t) {
     const size_t ti = (size_t)t * N + (size_t)i;
@@ -175,19 +175,10 @@ __global__ __launch_bounds__(64) void k_env_quad(VehArgs V, EnvArgs E, int T, ui
     if (EXTERNAL) {
       a0 = (valid && acts) ? O.act[ra0 * TN + ti] : 0.0f;
       a1 = (valid && acts) ? O.act[ra1 * TN + ti] : 0.0f;
-    } else {        // words (x, y) (even c) or (z, w) of Philox block c / 2 of this step
-      if ((t & 1) == 0) {   // even lanes draw the block of step t, odd lanes that of t + 1
-        const bool odd = c & 1;
-        const U4 r = philox(U4{gid, gstep0 + (uint32_t)t + (odd ? 1u : 0u), 1u, (uint32_t)(c >> 1)}, E.key0, E.key1);
-        const uint32_t g0 = quad_swap1(odd ? r.x : r.z), g1 = quad_swap1(odd ? r.y : r.w);
-        a0 = acts ? 2.0f * u01(odd ? g0 : r.x) - 1.0f : 0.0f;
-        a1 = acts ? 2.0f * u01(odd ? g1 : r.y) - 1.0f : 0.0f;
-        na0 = acts ? 2.0f * u01(odd ? r.z : g0) - 1.0f : 0.0f;
-        na1 = acts ? 2.0f * u01(odd ? r.w : g1) - 1.0f : 0.0f;
-      } else {
-        a0 = na0;
-        a1 = na1;
-      }
+    } else {
+      RW.advance(E, c, gid, gstep0, t, 1u);
+      a0 = acts ? 2.0f * u01(RW.w0) - 1.0f : 0.0f;
+      a1 = acts ? 2.0f * u01(RW.w1) - 1.0f : 0.0f;
       if (O.act && valid && acts) {
         O.act[ra0 * TN + ti] = a0;
         O.act[ra1 * TN + ti] = a1;

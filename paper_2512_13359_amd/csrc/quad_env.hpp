@@ -337,6 +337,29 @@ __device__ __forceinline__ void wrench(const float Tf[8], const float Tm[8], flo
 }
 
 
+// ------------------------------------------------------ random words by step ----
+// Words (x, y) (even c) or (z, w) of Philox block c / 2 of each control step, counter (env, step,
+// tag, block).  At an even step of the launch the even lanes draw that step's block and the odd
+// lanes the next step's, instead of each pair of lanes drawing the same block twice.
+struct StepWords {
+  uint32_t w0, w1;     // this step's
+  uint32_t n0, n1;     // the next step's, drawn at an even step
+  __device__ __forceinline__ void advance(const EnvArgs& E, int c, uint32_t gid, uint32_t gstep0, int t, uint32_t tag) {
+    if (t & 1) {
+      w0 = n0;
+      w1 = n1;
+      return;
+    }
+    const uint32_t odd = (uint32_t)(c & 1);
+    const U4 r = philox(U4{gid, gstep0 + (uint32_t)t + odd, tag, (uint32_t)(c >> 1)}, E.key0, E.key1);
+    const uint32_t g0 = quad_swap1(odd ? r.x : r.z), g1 = quad_swap1(odd ? r.y : r.w);
+    w0 = odd ? g0 : r.x;
+    w1 = odd ? g1 : r.y;
+    n0 = odd ? r.z : g0;
+    n1 = odd ? r.w : g1;
+  }
+};
+
 // ------------------------------------------------------ allocation table in LDS ----
 // Rows c = 0..2: force row c, rows 4 + c: moment row c, each x f_max; rows 3 and 7 zero
 // (lane 3 of a quad reads them).  Written by the first 64 threads of the block.
