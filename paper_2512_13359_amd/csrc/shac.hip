@@ -103,6 +103,7 @@ struct Lds {
                               // (forward), q(dz2) (reverse)
   float GX[WAVES][EPG][16];   // input-gradient partials of each wave (inputs 0..15)
   float pw[MAX_H + 1];        // gamma^t
+  float2 NZ[2][4][64];        // [step group t / 4, alternate][step][physics lane] action noise
 };
 static_assert(sizeof(Lds) <= 160 * 1024, "window kernel LDS exceeds a CU's 160 KB");
 
@@ -549,6 +550,15 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
   const size_t at0 = (size_t)grp * 64 + lane;
   auto rec_at = [&](int t, int s, int stage) { return A.rec + (((size_t)t * E.substeps + s) * 4 + stage) * G * 64 + at0; };
   auto row_at = [&](f32x4* a, int t) { return a + (size_t)t * G * 64 + at0; };
+  // Action noise, four steps at a time: wave w draws that of step t - t % 4 + w for every wave (each
+  // drawing all of it for itself, a Philox block and a Box-Muller pair per step and sweep, 4096
+  // environments x 32 steps with the actor's step took 390 us, so 384).  Read after the step's next barrier.
+  auto deal_noise = [&](int t) {
+    float e0, e1;
+    paper_noise(E, gid, A.step0 + (uint32_t)((t & ~3) + w), c, e0, e1);
+    S.NZ[(t >> 2) & 1][w][lane] = float2{e0, e1};
+  };
+  auto noise_at = [&](int t) { return S.NZ[(t >> 2) & 1][t & 3][lane]; };
   auto h2_at = [&](int t) { return A.h2s + (((size_t)t * G + grp) * WAVES + w) * H2_F4 + lane; };
 
   // ---------------------------------------------------------------- forward sweep
@@ -576,14 +586,14 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
       for (int m = 0; m < 4; ++m) hs[m * 64] = h2[m];
       const int b = t & 1;
       if (g < 2) *reinterpret_cast<f32x4*>(&S.Y[b][w][r][4 * g]) = y;
+      if (MODE == MODE_SAMPLE && (t & 3) == 0) deal_noise(t);
       wg_sync();
       a0 = c < 3 ? out_sum(S, b, slot, min(c, 2)) + b30 : 0.0f;
       a1 = c < 3 ? out_sum(S, b, slot, 3 + min(c, 2)) + b31 : 0.0f;
       if (MODE == MODE_SAMPLE) {
-        float e0, e1;
-        paper_noise(E, gid, A.step0 + (uint32_t)t, c, e0, e1);
-        a0 = __builtin_fmaf(sig0, e0, a0);
-        a1 = __builtin_fmaf(sig1, e1, a1);
+        const float2 e = noise_at(t);
+        a0 = __builtin_fmaf(sig0, e.x, a0);
+        a1 = __builtin_fmaf(sig1, e.y, a1);
       }
     }
     if (w == 0) {
@@ -774,12 +784,7 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
     go[0] = go[1] = go[2] = go[3] = 0.0f;
     const qadj::QObsK<float> ok{okv.x, okv.y, okv.z, okv.w};
     if (MODE != MODE_EXTERNAL) {
-      if (MODE == MODE_SAMPLE) {
-        float e0, e1;
-        paper_noise(E, gid, A.step0 + (uint32_t)t, c, e0, e1);
-        gls0 = __builtin_fmaf(ga0 * sig0, e0, gls0);
-        gls1 = __builtin_fmaf(ga1 * sig1, e1, gls1);
-      }
+      if (MODE == MODE_SAMPLE && ((t & 3) == 3 || t == h - 1)) deal_noise(t);
       // the policy's input gradient at o_t = o(s_t)
       lds_sync();
       put_inputs(S, w, lane, ok.dpb, ok.rv, x0.v, x0.w);
@@ -788,6 +793,11 @@ __global__ __launch_bounds__(64 * WAVES, 1) void k_window(EnvArgs E, VehArgs V, 
       const bf16x8 X = input_frag(S, w, lane), GY = gy_frag(S, w, lane);
       H.tile = (size_t)t * G + grp;
       mlp_backward(ob, &S.W[w][0][0], X, GY, h2, w, lane, S, H, sums, go);
+      if (MODE == MODE_SAMPLE) {   // after the exchanges of the backward pass
+        const float2 e = noise_at(t);
+        gls0 = __builtin_fmaf(ga0 * sig0, e.x, gls0);
+        gls1 = __builtin_fmaf(ga1 * sig1, e.y, gls1);
+      }
     }
     cr = (valid && t > 0) ? -S.pw[t > 0 ? t - 1 : 0] * A.inv_nh : 0.0f;
     through_obs(t - 1, cr, ok, pt, x0);
