@@ -190,7 +190,8 @@ int auv_rollout_static(auv_env* env, int32_t T, int mode, const auv_mlp* policy,
 
 /* Generalised advantage estimation over a [T][N] rollout (backward scan per env):
  * delta_t = r_t + gamma (1 - d_t) V_{t+1} - V_t, V_T = last_value;
- * A_t = delta_t + gamma lambda (1 - d_t) A_{t+1}, A_T = 0; ret_t = A_t + V_t. */
+ * A_t = delta_t + gamma lambda (1 - d_t) A_{t+1}, A_T = 0; ret_t = A_t + V_t.
+ * adv and ret may be the buffers of reward, value or done themselves (in place). */
 int auv_gae(int32_t T, int32_t n_envs, const float* reward, const float* value,
             const float* done, const float* last_value, float gamma, float lambda,
             float* adv, float* ret, void* stream);

@@ -295,16 +295,17 @@ __global__ __launch_bounds__(64 * RED_WAVES) void k_stats_reduce(const float* __
 // spread over many lanes and every load of a round is issued at once; the segments exchange
 // (alpha, beta) of their first step through LDS, and each folds the later segments, last one
 // first, into the A that enters its own.  Rounds run from the last steps to the first; the A
-// that leaves a round (the same fold carried on to segment 0) enters the one before it.
+// that leaves a round (the same fold carried on to segment 0) and its first value enter the one
+// before it.  A round reads only its own steps, all of them before it writes any, so adv and ret
+// may be reward, value or done itself.
 // Bound by HBM (20 B per environment-step): 4096 x 1000 in 20 us, 4.1 TB/s; one lane per
 // environment with the scan's steps in series, which this replaced above 512 steps, took 117 us.
 template <int L, int E>
-__global__ __launch_bounds__(1024) void k_gae_seg(int T, int n, const float* __restrict__ rew,
-                                                  const float* __restrict__ val, const float* __restrict__ dn,
-                                                  const float* __restrict__ last, float gamma, float gl,
-                                                  float* __restrict__ adv, float* __restrict__ ret) {
+__global__ __launch_bounds__(1024) void k_gae_seg(int T, int n, const float* rew, const float* val, const float* dn,
+                                                  const float* last, float gamma, float gl, float* adv, float* ret) {
   constexpr int SPW = 64 / E;                // segments per wave
   __shared__ float2 pair[2][16 * SPW][E];    // by round parity: read in a round, written again two rounds on
+  __shared__ float first[2][E];              // a round's first value, read in the next one
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, S = SPW * (blockDim.x >> 6);
   const int e = lane % E, seg = SPW * w + lane / E;
   const int i = blockIdx.x * E + e;
@@ -312,7 +313,8 @@ __global__ __launch_bounds__(1024) void k_gae_seg(int T, int n, const float* __r
   const size_t N = (size_t)n, ic = (size_t)(valid ? i : n - 1);
   const int span = S * L;
   float carry = 0.0f;                        // A entering the round from the later steps
-  for (int round = (T - 1) / span; round >= 0; --round) {
+  const int rounds = (T - 1) / span + 1;
+  for (int round = rounds - 1; round >= 0; --round) {
     const int t0 = round * span + seg * L, t1 = min(T, t0 + L);
     float r[L], v[L], d[L];
 #pragma unroll
@@ -322,7 +324,9 @@ __global__ __launch_bounds__(1024) void k_gae_seg(int T, int n, const float* __r
       v[k] = val[ti];
       d[k] = dn[ti];
     }
-    float vnext = t1 < T ? val[(size_t)t1 * N + ic] : last[ic];
+    float vnext = (seg == S - 1 && round < rounds - 1) ? first[(round + 1) & 1][e]
+                                                       : (t1 < T ? val[(size_t)t1 * N + ic] : last[ic]);
+    if (seg == 0) first[round & 1][e] = v[0];
     float a = 0.0f, b = 1.0f;
 #pragma unroll
     for (int k = L - 1; k >= 0; --k) {

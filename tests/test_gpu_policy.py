@@ -371,6 +371,26 @@ def test_gae_sizes(n, T):
     assert np.abs(host(ret) - q).max() <= bound
 
 
+@pytest.mark.parametrize("n, T", [(300, 513), (16384, 257), (256, 1025), (17, 3000)])
+def test_gae_in_place(n, T):
+    """Results written over the inputs (ret over the values, adv over the rewards, and the other
+    way round) past one round of the scan have the bits of results written apart."""
+    from paper_2512_13359_amd import _abi as A
+    announce(f"gae in place n={n} T={T}")
+    g = torch.Generator(device="cuda").manual_seed(n + T)
+    rew, val = (torch.randn(T, n, device="cuda", generator=g) for _ in range(2))
+    done = (torch.rand(T, n, device="cuda", generator=g) < 0.01).float()
+    last = torch.randn(n, device="cuda", generator=g)
+    adv, ret = torch.empty_like(rew), torch.empty_like(rew)
+    A.auv_gae(T, n, rew, val, done, last, 0.99, 0.95, adv, ret)
+    for over in ("ret=value", "adv=value", "adv=reward, ret=value", "adv=value, ret=reward"):
+        r, v = rew.clone(), val.clone()
+        a = r if "adv=reward" in over else (v if "adv=value" in over else torch.empty_like(r))
+        q = v if "ret=value" in over else (r if "ret=reward" in over else torch.empty_like(r))
+        A.auv_gae(T, n, r, v, done, last, 0.99, 0.95, a, q)
+        assert torch.equal(a, adv) and torch.equal(q, ret), over
+
+
 @pytest.mark.parametrize("n_out", [1, 8])
 def test_mlp_forward_independent_of_batch(n_out):
     """A sample's output has the same bits in a batch that gives every wave several groups as in
