@@ -324,8 +324,10 @@ __global__ __launch_bounds__(1024) void k_gae_seg(int T, int n, const float* rew
       v[k] = val[ti];
       d[k] = dn[ti];
     }
-    float vnext = (seg == S - 1 && round < rounds - 1) ? first[(round + 1) & 1][e]
-                                                       : (t1 < T ? val[(size_t)t1 * N + ic] : last[ic]);
+    const bool carried = seg == S - 1 && round < rounds - 1;   // its next step is the later round's first
+    const float vn = *(t1 < T ? val + (size_t)(carried ? t1 - 1 : t1) * N + ic : last + ic);
+    const float vc = first[(round + 1) & 1][e];
+    float vnext = carried ? vc : vn;
     if (seg == 0) first[round & 1][e] = v[0];
     float a = 0.0f, b = 1.0f;
 #pragma unroll
