@@ -290,8 +290,8 @@ __global__ __launch_bounds__(64 * RED_WAVES) void k_stats_reduce(const float* __
 // Segmented backward GAE.  The recursion A_t = delta_t + c_t A_{t+1}, with c_t = gamma lambda
 // (1 - d_t) and delta_t = r_t + gamma (1 - d_t) V_{t+1} - V_t, is linear in A: over a segment
 // of steps [t0, t1) it gives A_t = alpha_t + beta_t A_{t1}, alpha from the recursion started
-// at 0, beta_t = c_t ... c_{t1-1}.  A workgroup takes E environments (lane mod E) and, per
-// round, S = (64 / E) waves segments of L steps each, so that the scan of one environment is
+// at 0, beta_t = c_t ... c_{t1-1}.  A workgroup takes E environments (thread mod E) and, per
+// round, S = threads / E segments of L steps each, so that the scan of one environment is
 // spread over many lanes and every load of a round is issued at once; the segments exchange
 // (alpha, beta) of their first step through LDS, and each folds the later segments, last one
 // first, into the A that enters its own.  Rounds run from the last steps to the first; the A
@@ -303,12 +303,15 @@ __global__ __launch_bounds__(64 * RED_WAVES) void k_stats_reduce(const float* __
 template <int L, int E>
 __global__ __launch_bounds__(1024) void k_gae_seg(int T, int n, const float* rew, const float* val, const float* dn,
                                                   const float* last, float gamma, float gl, float* adv, float* ret) {
-  constexpr int SPW = 64 / E;                // segments per wave
-  __shared__ float2 pair[2][16 * SPW][E];    // by round parity: read in a round, written again two rounds on
+  __shared__ float2 pair[2][1024 / E][E];    // by round parity: read in a round, written again two rounds on
   __shared__ float first[2][E];              // a round's first value, read in the next one
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, S = SPW * (blockDim.x >> 6);
-  const int e = lane % E, seg = SPW * w + lane / E;
-  const int i = blockIdx.x * E + e;
+  const int S = blockDim.x / E;
+  const int e = threadIdx.x % E, seg = threadIdx.x / E;
+  // E > 64: neighbouring workgroups on one XCD (the dispatcher deals them out in turn), where the
+  // two parts of a cache line that rows of an odd length leave to both meet in one L2
+  const int bid = blockIdx.x, x = bid & 7, per = gridDim.x >> 3;
+  const int wg = E > 64 ? x * per + min(x, (int)(gridDim.x & 7)) + (bid >> 3) : bid;
+  const int i = wg * E + e;
   const bool valid = i < n;
   const size_t N = (size_t)n, ic = (size_t)(valid ? i : n - 1);
   const int span = S * L;
@@ -782,16 +785,21 @@ int auv_gae(int32_t T, int32_t n_envs, const float* reward, const float* value, 
   hipStream_t s = (hipStream_t)stream;
   const float gl = gamma * lambda;
   auto launch = [&](auto kernel, int L, int E) {
-    const int spw = 64 / E, waves = std::min(16, (T + L * spw - 1) / (L * spw));
-    hipLaunchKernelGGL(kernel, dim3((n_envs + E - 1) / E), dim3(64 * waves), 0, s, T, n_envs, reward, value, done,
-                       last_value, gamma, gl, adv, ret);
+    const int segs = std::min(1024 / E, (T - 1) / L + 1);
+    hipLaunchKernelGGL(kernel, dim3((n_envs - 1) / E + 1), dim3((segs * E + 63) / 64 * 64), 0, s, T, n_envs, reward,
+                       value, done, last_value, gamma, gl, adv, ret);
   };
   // 64 environments per workgroup read whole 256-byte rows and win once that gives every CU a
   // workgroup (16384 x 1000: 62 us, with 32 per workgroup 71 us); below, 32 give twice the
   // workgroups and twice the segments (4096 x 1000: 20 us against 24; 4096 x 512: 9.2 against
   // 12.6), and 16 the shortest scan of a few environments (64 x 4000: 23 us against 38; at 512 x
   // 2000 no longer faster).  Segments of 32 steps were slower everywhere (4096 x 1000: 28-40 us).
-  if (n_envs >= 64 * compute_units())
+  // Past a round of those, at environments that fill three quarters of the CUs with 256 each,
+  // these: pieces of rows of 1 KB, which the memory likes better (65536 x 1000: 249 us against 266;
+  // 60001 x 1000: 226 against 358; 131071 x 600: 327 against 460; at 32768 x 1000 159 against 134).
+  if (T > 256 && n_envs >= 192 * compute_units())
+    launch(k_gae_seg<8, 256>, 8, 256);
+  else if (n_envs >= 64 * compute_units())
     launch(k_gae_seg<16, 64>, 16, 64);
   else if (n_envs > 256)
     launch(k_gae_seg<16, 32>, 16, 32);

@@ -351,9 +351,9 @@ def test_two_tile_rollout_parity(nets):
 
 
 @pytest.mark.parametrize("n,T", [(1, 1), (256, 1025), (16, 2049), (257, 512), (300, 513), (1000, 1100), (16385, 256),
-                                 (16384, 257)])
+                                 (16384, 257), (49151, 257), (49152, 257), (65537, 300)])
 def test_gae_sizes(n, T):
-    """Each number of environments per workgroup (16, 32, 64) at and past one round of the
+    """Each number of environments per workgroup (16, 32, 64, 256) at and past one round of the
     segmented scan, against the oracle.  Every step adds at most six roundings of values within
     the result's scale, and each decays by gamma lambda, so 6 x 2^-24 / (1 - 0.9405) of it."""
     from paper_2512_13359_amd import _abi as A
@@ -371,7 +371,7 @@ def test_gae_sizes(n, T):
     assert np.abs(host(ret) - q).max() <= bound
 
 
-@pytest.mark.parametrize("n, T", [(300, 513), (16384, 257), (256, 1025), (17, 3000)])
+@pytest.mark.parametrize("n, T", [(300, 513), (16384, 257), (256, 1025), (17, 3000), (49409, 263)])
 def test_gae_in_place(n, T):
     """Results written over the inputs (ret over the values, adv over the rewards, and the other
     way round) past one round of the scan have the bits of results written apart."""
