@@ -63,6 +63,7 @@ __device__ __forceinline__ void stats_row_combine(RolloutShared& S, StatsBuf& B,
   const size_t G = gridDim.x;
   if (TPW == 1) {
     if (lane <= slot) {
+      asm volatile("" : "+v"(lane));   // addresses formed here: kept over the steps, they were spilled
 #pragma unroll
       for (int s = 0; s < 3; ++s) work[((size_t)s * G + blockIdx.x) * T + t0 + lane] = B.v[s];
     }
@@ -77,6 +78,7 @@ __device__ __forceinline__ void stats_row_combine(RolloutShared& S, StatsBuf& B,
   if ((before + 1u) % (unsigned)TPW != 0u) return;   // not the last tile of this row
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
   if (lane <= slot) {
+    asm volatile("" : "+v"(lane));
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
       float v = S.st[par][0][s][lane];

@@ -400,18 +400,23 @@ template <bool PAPER = false>
 __device__ __forceinline__ void load_buffers(const EnvArgs& E, int c, int i, bool valid, QEnv& X, Params& P) {
   const int cv = c < 3 ? c : 0;   // a valid row for lane 3's loads
   const size_t N = (size_t)E.n;
+  // the idle state first and the buffers over it: with a branch for each, their last stores, to
+  // two members, became one through a pointer, which kept both members in scratch memory
+  X.p = X.v = X.om = X.u0 = X.u1 = 0.0f;
+  X.q = c == 3 ? 1.0f : 0.0f;
+  X.ep = 0;
+  X.episode = 0;
+  X.ob = QObs{0, 0, 0};
   if (valid) {
     X.p = c < 3 ? E.state[cv * N + i] : 0.0f;
     X.q = E.state[(c < 3 ? 4 + c : 3) * N + i];
     X.v = c < 3 ? E.state[(7 + cv) * N + i] : 0.0f;
     X.om = c < 3 ? E.state[(10 + cv) * N + i] : 0.0f;
-    load_params(E.params, E.n, i, P);
     X.ep = E.ep_step[i];
     X.episode = E.episode[i];
     X.ob.dpb = c < 3 ? E.obs[cv * N + i] : 0.0f;
     X.ob.c0 = c < 3 ? E.obs[(3 + cv) * N + i] : 0.0f;
     if (PAPER) {
-      X.ob.c1 = 0.0f;
       X.u0 = c < 3 ? E.obs[(12 + cv) * N + i] : 0.0f;
       X.u1 = c < 3 ? E.obs[(15 + cv) * N + i] : 0.0f;
     } else {
@@ -419,13 +424,9 @@ __device__ __forceinline__ void load_buffers(const EnvArgs& E, int c, int i, boo
       X.u0 = E.obs[(15 + 2 * c) * N + i];
       X.u1 = E.obs[(16 + 2 * c) * N + i];
     }
+    load_params(E.params, E.n, i, P);
   } else {
-    X.p = X.v = X.om = X.u0 = X.u1 = 0.0f;
-    X.q = c == 3 ? 1.0f : 0.0f;
-    X.ep = 0;
-    X.episode = 0;
     P = Params{{1, 1, 1}, {0, 0, 0}, {0, 0, 0}, {1, 0, 0, 0}, {0, 0, 0}, {0, 0, 0}, {0, 0, 0}, 0, 0};
-    X.ob = QObs{0, 0, 0};
   }
 }
 
