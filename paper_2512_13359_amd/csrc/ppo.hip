@@ -932,11 +932,10 @@ struct WgShared {
 // 1 KB from memory to LDS: lane l's 16 bytes to dst + 16 l (dst wave-uniform).  Written as
 // assembly: the compiler takes every LDS read as depending on the builtin's loads and waits for
 // all of them, prefetches included.  The program waits for them itself (wait_loads, then a
-// barrier); the assembly writes no register but M0, which this target's other instructions
-// here do not use.
+// barrier); the assembly writes no register but M0.
 __device__ __forceinline__ void load_lds(const char* src, char* dst) {
   const uint32_t off = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)dst;
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(off) : "memory");
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(off) : "m0", "memory");
 }
 
 template <int N>

@@ -1,5 +1,9 @@
-"""Scratch memory of the built kernels, from the metadata of libauv.so: a kernel that keeps values
-in memory between the steps of a loop waits for them there, behind its own stores."""
+"""What the kernels' machine code holds of the chip, checked without a GPU.
+
+Scratch memory of the built kernels, from the metadata of libauv.so (a kernel that keeps values in
+memory between the steps of a loop waits for them there, behind its own stores); and that the
+sources' assembly names the special register it writes, which the compiler uses too."""
+import glob
 import os
 import re
 import shutil
@@ -34,3 +38,13 @@ def test_no_scratch(scratch, kernel, forms):
     found = {n: b for n, b in scratch.items() if kernel in n}
     assert len(found) == forms
     assert not any(found.values()), {n: b for n, b in found.items() if b}
+
+
+def test_assembly_names_m0():
+    found = 0
+    for path in glob.glob(os.path.join(ROOT, "paper_2512_13359_amd", "csrc", "*.h*")):
+        for stmt in re.findall(r"\basm\b[^;]*;", open(path).read()):
+            if re.search(r"s_mov_b32 m0\b", stmt):
+                found += 1
+                assert '"m0"' in stmt, (path, stmt)
+    assert found == 1
