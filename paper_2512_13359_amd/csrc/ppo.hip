@@ -935,7 +935,10 @@ struct WgShared {
 // barrier); the assembly writes no register but M0.
 __device__ __forceinline__ void load_lds(const char* src, char* dst) {
   const uint32_t off = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)dst;
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // M0 is a register that the compiler writes itself
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(off) : "m0", "memory");
+#pragma clang diagnostic pop
 }
 
 template <int N>
