@@ -354,7 +354,8 @@ typedef struct {
 } auv_ppo_net;
 
 /* Bytes of device workspace auv_ppo_grad needs for a minibatch of B samples (-1 for B
- * outside [1, 2^24]); about 1.1 KB per sample from B = 131072 up, 1.6 KB below, plus 80 MB. */
+ * outside [1, 2^24]); about 1.6 KB per sample, 1.1 KB from B = 131072 up, 0.6 KB (but no less
+ * than 210 MB) from 196608 up, plus 80 MB. */
 int64_t auv_ppo_work_bytes(int32_t B);
 
 /* Loss and gradients of one minibatch: entries idx[0..B-1] (int32 sample indices into the

@@ -95,18 +95,24 @@ inline int padded(int B) { return (B + 32 * DW2_DEPTH - 1) / (32 * DW2_DEPTH) * 
 inline int nparam(int n_out) { return HID * 23 + HID * HID + n_out * HID + 2 * HID + n_out + (n_out == 8 ? 8 : 0); }
 inline int red_blocks(int n_out) { return (nparam(n_out) + RED_ELEMS - 1) / RED_ELEMS; }
 
-// Byte offsets of the workspace parts for a minibatch of B; returns the total.
 // From this many 32-sample steps on, k_vwgrad recomputes q(h1) instead of reading it.
 constexpr int VW_RECOMP_STEPS = 4096;
+// Steps from which the value net's gradient (in an update of both networks and alone: the two have
+// the same bits) is formed like the policy's.  Below, its input gradient stays in k_vtile: a critic's
+// fit repeats it in a chain of updates, in which another order of its sums grows to half a percent
+// of the last gradient's norm (64 updates of 32768 samples; more than the two are allowed to be
+// apart in perf/cases.py), though k_wgrad would be 7 % faster there.
+constexpr int VALUE_LATER_STEPS = 6144;
 constexpr int WORK_PARTS = 14;
+// Byte offsets of the workspace parts for a minibatch of B; returns the total.
 inline size_t work_layout(int B, size_t off[WORK_PARTS]) {
   const size_t Bp = (size_t)padded(B), G = MAX_GROUPS;
-  const bool recomp = (int)(Bp / 32) >= VW_RECOMP_STEPS;
+  const bool later = (int)(Bp / 32) >= VALUE_LATER_STEPS, recomp = (int)(Bp / 32) >= VW_RECOMP_STEPS;
   const size_t sizes[WORK_PARTS] = {2 * sizeof(double) * ADV_BLOCKS, Bp * HID * 2,
                             G * 8 * HID * 4, G * HID * 4, G * 16 * 4, G * 16 * 4, 2 * G * STATS * 4,
                             G * HID * 32 * 4, G * HID * 4, G * HID * HID * 4,
                             2 * (size_t)red_blocks(8) * 4,
-                            Bp / 16 * 64 * 16, Bp * HID * 2, recomp ? 0 : Bp * HID * 2};
+                            Bp / 16 * 64 * 16, later ? 0 : Bp * HID * 2, recomp ? 0 : Bp * HID * 2};
   size_t o = 0;
   for (int k = 0; k < WORK_PARTS; ++k) {
     off[k] = o;
@@ -312,12 +318,6 @@ constexpr int VT_WAVES = 8;
 // k_vtile's input gradient (dz1): left to k_wgrad; or formed in it from the tile's own dz2, q(dz1)
 // stored, and without or with q(h1) stored (the value net below VALUE_LATER_STEPS, see k_vwgrad)
 constexpr int DX_LATER = 0, DX_RECOMP = 1, DX_STORE = 2;
-// Steps from which the value net's gradient (in an update of both networks and alone: the two have
-// the same bits) is formed like the policy's.  Below, its input gradient stays in k_vtile: a critic's
-// fit repeats it in a chain of updates, in which another order of its sums grows to a percent of
-// the last gradient's norm (64 updates of 32768 samples), so that the results of a seed would
-// change; k_wgrad would be 6 % faster there.
-constexpr int VALUE_LATER_STEPS = 6144;
 
 struct VtWeights {
   bf16x8 w1[16][64];      // layer 1 A fragments [M-tile][lane] (K = the 32 padded inputs)
@@ -1698,8 +1698,12 @@ extern "C" {
 
 int64_t auv_ppo_work_bytes(int32_t B) {
   if (B < 1 || B > PPO_MAX_B) return -1;
-  size_t off[ppo::WORK_PARTS];
-  return (int64_t)ppo::work_layout(B, off);
+  using namespace ppo;
+  size_t off[WORK_PARTS];
+  size_t n = work_layout(B, off);
+  // enough for the smaller minibatches too, some of which keep more per sample
+  if (padded(B) / 32 >= VALUE_LATER_STEPS) n = std::max(n, work_layout(32 * VALUE_LATER_STEPS - 128, off));
+  return (int64_t)n;
 }
 
 int auv_ppo_grad(const auv_ppo_config* cfg, const auv_mlp* policy, const auv_mlp* value, const auv_ppo_batch* batch,

@@ -102,6 +102,16 @@ def test_argument_errors_before_any_launch():
     assert A.auv_stats_work_floats(65, 2) == 3 * 2 * 4 * 2
 
 
+def test_ppo_workspace_sizes():
+    """auv_ppo_work_bytes: from 196608 samples up no room for operands that no kernel stores there,
+    and still enough for every smaller minibatch."""
+    from paper_2512_13359_amd import _abi as A
+    assert A.auv_ppo_work_bytes(1 << 24) < 0.6 * 1024 * (1 << 24) + 81e6
+    below = max(A.auv_ppo_work_bytes(B) for B in (1, 4096, 131071, 131072, 196479, 196480))
+    sizes = [A.auv_ppo_work_bytes(B) for B in (196481, 196608, 262144, 500000, 1 << 24)]
+    assert below <= sizes[0] and sizes == sorted(sizes)
+
+
 def test_value_regression_sizes_and_argument_errors():
     """auv_ppo_fit_work_bytes: -1 outside 16 <= M <= 2^28, 1 <= batches <= M / 16; else the
     minibatch workspace plus two index slots.  auv_ppo_fit_value rejects bad arguments on the
