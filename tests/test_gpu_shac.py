@@ -363,27 +363,31 @@ def test_shac_full_size_sampled_envs():
     assert _block_err(ga[:, :, idx], want["grad_act"] * scale) <= 5e-2
 
 
-def test_shac_more_groups_than_workgroups():
+@pytest.mark.parametrize("n, ends", [(8192, False), (4170, False), (4170, True)])
+def test_shac_more_groups_than_workgroups(n, ends):
     """8192 environments are two 16-environment groups for each of 256 workgroups, which then run
-    in turn and add up the small gradients of both.  Each half as a handle of its own gives every
+    in turn and add up the small gradients of both; 4170 are two for some workgroups and one for
+    the rest, the last group of ten environments; with `ends` the window ends every episode, so
+    that a group is reset before the next one runs.  Each half as a handle of its own gives every
     environment the same bits (the objective's weight is exactly doubled), and the mean of
     the halves' gradients up to the order of fp32 sums."""
-    n, h = 8192, 3
-    announce(f"SHAC grouped window n={n}")
+    h = 3
+    announce(f"SHAC grouped window n={n} ends={ends}")
     require_gpu()
     x0 = torch.from_numpy(W.random_states(n, seed=4))
 
     def run(off, m):
-        g = gpu_env(W.config("c6", n_envs=m, env_offset=off))
+        g = gpu_env(W.config("c6", n_envs=m, env_offset=off, **(dict(episode_len=h) if ends else {})))
         g.set_task(W.PAPER_TASK)
         g.reset()
         g.state.copy_(x0[:, off:off + m])
         L = _learner(g, h)
         out = dict(act=_dev(8, h, m), grad_act=_dev(8, h, m), grad_state0=_dev(13, m), value_last=_dev(m))
         L.window(out=out)
-        return L.grad.clone(), dict(out, state=g.state, params=g.params)
+        return L.grad.clone(), dict(out, state=g.state, params=g.params, episode=g.episode)
 
     grad, full = run(0, n)
+    assert torch.equal(full["episode"], torch.full_like(full["episode"], int(ends)))
     halves = [run(0, n // 2), run(n // 2, n // 2)]
     for k, v in full.items():
         both = torch.cat([q[k] for _, q in halves], dim=-1)
