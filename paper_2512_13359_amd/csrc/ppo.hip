@@ -1179,16 +1179,17 @@ inline int vt_groups(int tiles, int cus) {
 
 // Shape of the weight-gradient product by the minibatch's 32-sample steps.  From 6144 steps
 // (196608 samples) 128-column blocks of two tiles per wave, 128 chunks, 256 workgroups: an
-// update of 262144 samples takes 390 us, with 64-column blocks (one tile per wave, twice the LDS
-// reads per column) 416, with 256-column blocks (256 chunk partials, 64 MB) 419.  Below, 64-column
-// blocks of 8 to 64 chunks of eight steps or more, which have four workgroups per chunk: 131072
-// samples 244 us against 252, 32768 121 against 136; at 3000 samples chunks of eight steps take
-// 76 us per update, of 16 82.
+// update of 262144 samples took 390 us, with 64-column blocks (one tile per wave, twice the LDS
+// reads per column) 416, with 256-column blocks (256 chunk partials, 64 MB) 419 (the update's
+// other kernels have since become 35 us shorter).  Below, 64-column blocks of 8 to 64 chunks of
+// eight steps or more, which have four workgroups per chunk: 131072 samples 244 us against 252,
+// 32768 121 against 136; at 3000 samples chunks of eight steps take 76 us per update, of 16 82.
+constexpr int WIDE_STEPS = 6144;
 struct VwPlan {
   int cols, chunks;
 };
 inline VwPlan vw_plan(int steps) {
-  if (steps >= VALUE_LATER_STEPS) return {128, 128};
+  if (steps >= WIDE_STEPS) return {128, 128};
   const int c = (steps / 8 + 7) / 8 * 8;
   return {64, c < 8 ? 8 : (c > 64 ? 64 : c)};
 }
