@@ -29,8 +29,11 @@
 //                  form, every lane row a copy, and the RK4 stages re-integrated in the
 //                  reverse sweep, a 32-step window took 693 us in all; with four lanes per
 //                  environment 457 us; with the small weight gradients summed here, in place
-//                  of a kernel that read 200 MB of their operands back, 398 us.  Each wave adds its features' dW1, dW3 and bias
-//                  gradients up in registers and stores the bf16 operands of dW2 (q(h1),
+//                  of a kernel that read 200 MB of their operands back, 398 us; with the action
+//                  noise drawn once for the four waves 382 us.  Those sums' 48 accumulators are
+//                  live through both sweeps: the policy modes spill 30 registers (68 and 84 bytes
+//                  of scratch per lane; none before).  Each wave adds its features' dW1, dW3 and
+//                  bias gradients up in registers and stores the bf16 operands of dW2 (q(h1),
 //                  q(dz2)) as "half fragments"
 //   k_dw2          (PPO update) dW2 = sum q(dz2) q(h1)^T over all N h samples
 //   k_reduce       (PPO update) fixed-order sums of the partials -> packed gradient
@@ -82,9 +85,9 @@ struct WinArgs {
   float gamma;
   NetF pol, val;
   const float* log_std;
-  // per lane of the four-lane layout, [..][workgroup][lane]: rec [h][substeps][4 RK4 stages]
-  // (q, v, omega, and p in the first, 1 / |q| in the last), obk [h] (dpb, rotation vector, sk, kn), aa [h] (action components c and 3 + c
-  // before clipping, their moving averages before the step)
+  // per lane of the four-lane layout, [..][group][lane]: rec [h][substeps][4 RK4 stages] (q, v,
+  // omega, and p in the first, 1 / |q| in the last), obk [h] (dpb, rotation vector, sk, kn), aa [h]
+  // (action components c and 3 + c before clipping, their moving averages before the step)
   f32x4 *rec, *obk, *aa;
   float *J, *Jr, *vl;
   f32x4* h2s;                          // policy hidden-2 activations [h][G][wave][M-tile][lane]
