@@ -298,7 +298,7 @@ __global__ __launch_bounds__(64 * RED_WAVES) void k_stats_reduce(const float* __
 // that leaves a round (the same fold carried on to segment 0) and its first value enter the one
 // before it.  A round reads only its own steps, all of them before it writes any, so adv and ret
 // may be reward, value or done itself.
-// Bound by HBM (20 B per environment-step): 4096 x 1000 in 20 us, 4.1 TB/s; one lane per
+// Bound by HBM (20 B per environment-step): 4096 x 1000 in 19 us, 4.3 TB/s; one lane per
 // environment with the scan's steps in series, which this replaced above 512 steps, took 117 us.
 template <int L, int E>
 __global__ __launch_bounds__(1024) void k_gae_seg(int T, int n, const float* rew, const float* val, const float* dn,
@@ -794,9 +794,10 @@ int auv_gae(int32_t T, int32_t n_envs, const float* reward, const float* value, 
   // workgroups and twice the segments (4096 x 1000: 20 us against 24; 4096 x 512: 9.2 against
   // 12.6), and 16 the shortest scan of a few environments (64 x 4000: 23 us against 38; at 512 x
   // 2000 no longer faster).  Segments of 32 steps were slower everywhere (4096 x 1000: 28-40 us).
-  // Past a round of those, at environments that fill three quarters of the CUs with 256 each,
-  // these: pieces of rows of 1 KB, which the memory likes better (65536 x 1000: 249 us against 266;
-  // 60001 x 1000: 226 against 358; 131071 x 600: 327 against 460; at 32768 x 1000 159 against 134).
+  // Past a round of those, and from environments that fill three quarters of the CUs with 256
+  // each, these: rows in pieces of 1 KB (49152 x 1000: 188 us against 203 with 64 per workgroup;
+  // 65536 x 1000: 244 against 265; 60001 x 1000: 223 against 357; 131071 x 600: 332 against 463; at
+  // 32768 x 1000 159 against 134, and within one round 65536 x 64 15 against 13).
   if (T > 256 && n_envs >= 192 * compute_units())
     launch(k_gae_seg<8, 256>, 8, 256);
   else if (n_envs >= 64 * compute_units())
