@@ -514,9 +514,16 @@ __device__ __forceinline__ float lanes_sum_quads(float v, int lane) {
   const float up = dpp_move<DPP_ROW_ROR12>(v), down = dpp_move<DPP_ROW_ROR4>(v);
   v += (lane & 4) ? down : up;                // quad ^ 1
   v += dpp_move<DPP_ROW_ROR8>(v);             // quad ^ 2
-  v += __shfl_xor(v, 16);
-  v += __shfl_xor(v, 32);
-  return v;
+  // the rows through the VALU's lane swaps (two shuffles through LDS made a lone step with statistics
+  // 0.6 us longer): of two copies of v, one gets the even rows (halves) twice, the other the odd ones.
+  // Written as assembly, with the two wait states after the write of an operand: the compiler adds
+  // one result of its builtin twice.
+  float u = v;
+  asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(v), "+v"(u));
+  v += u;                                     // row ^ 1
+  u = v;
+  asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(v), "+v"(u));
+  return v + u;                               // row ^ 2
 }
 
 __device__ __forceinline__ uint32_t quad_swap1(uint32_t x) {   // the value of lane l ^ 1
